@@ -382,7 +382,8 @@ int ktmi_surface(ktmi_handle *h, const double *A, double tau_A, const double *B,
  * f = 1/(exp((p.u - mu)/T) + stat), df = (1 - stat f) p~_a p~_b pi~^{ab} / (2 T^2 e_plus_P)
  * (eps_plus_P = e + P at freeze-out in GeV/fm^3; 0 leaves delta f out).  out is
  * device memory; ws is caller-owned device scratch of ktmi_spectra_workspace_bytes
- * bytes.  The result does not depend on scheduling (fixed summation order).
+ * bytes (a smaller one is taken too if it holds one partial result per 256 elements, at
+ * most 64 of them; the sums are then split less).  The result does not depend on scheduling (fixed summation order).
  * Synchronises stream once (upload of the small tables), then runs async on it.
  * KTMI_EINVAL on bad arguments or a short workspace. */
 size_t ktmi_spectra_workspace_bytes(long n, int ns, int nY, int npt, int nphi);

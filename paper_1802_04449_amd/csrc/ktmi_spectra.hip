@@ -9,16 +9,33 @@
 // p.u = p~^tau u~^tau - p~^x u~^x - p~^y u~^y - p~^eta u~^eta,
 // f = 1 / (exp((p.u - mu)/T) + sigma), df = (1 - sigma f) p~_a p~_b pi~^{ab} / (2 T^2 (e + P)).
 //
-// Layout of the work: a thread owns kPhi consecutive phi bins of one (species, Y,
-// pT); a workgroup holds 256 such threads and one slice of the elements, which it
-// streams through LDS in chunks (every element is read from memory once per
-// workgroup and used by all its bins).  Slices give the chip enough workgroups;
-// their partial sums are added in slice order by a second kernel, so the result
-// does not depend on scheduling.
+// The exponential factorises: with x_L = (p~^tau u~^tau - p~^eta u~^eta - mu)/T, which
+// depends on (species, Y, pT), and x_T = -(p~^x u~^x + p~^y u~^y)/T, which depends on
+// (pT, phi), exp((p.u - mu)/T) = e^{x_L} e^{x_T}; p.dSigma and p~p~pi~ split the same
+// way into a longitudinal part, a transverse part and (pi~ only) p~^tau and p~^eta
+// times two transverse sums.  A workgroup therefore computes, per element, one record
+// for each of its (species, Y, pT) and one for each of its (pT, phi), stages both in
+// LDS, and every thread evaluates a small outer product of them: per bin one product
+// for the exponential, one reciprocal and a few multiply-adds, instead of an
+// exponential, a division and the whole quadratic form.
+//
+// Layout of the work: a thread owns TS (species, Y) pairs x TP phi bins of one pT; 16
+// lanes run over the pairs and 16 slots over groups of TP phi bins (of any pT), so a
+// workgroup of 256 covers 16 TS pairs x 16 TP transverse bins and one slice of the
+// elements.  Slices give the chip enough workgroups; their partial sums are added in
+// slice order by a second kernel, so the result does not depend on scheduling.
+//
+// Bound by FP64 VALU issue: about 21 instruction slots per (element, bin), the
+// reciprocal four of them, plus a sixth for the records (FP64 instructions issue at
+// 0.7-0.85 of the nominal one per CU and clock under this load).  41660 elements x 8
+// species x 41 x 15 x 48 bins with delta f: 23.0 ms -> 9.06 ms a call (4.3e11 -> 1.09e12
+// element-bin evaluations/s); an exponential and a division per bin took about 80
+// slots.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "../../include/ktmi.h"
@@ -29,109 +46,207 @@ namespace ktmi {
 namespace {
 
 constexpr int kSpecBlock = 256;
-#ifndef KTMI_SPEC_PHI
-#define KTMI_SPEC_PHI 16
-#endif
-// phi bins per thread; on the 201x201x105 benchmark surface (41660 elements, 8
-// species, 41 x 15 x 48 bins): 4 -> 30.0 ms, 8 -> 24.4 ms, 16 -> 23.7 ms
-constexpr int kPhi = KTMI_SPEC_PHI;
-constexpr int kChunk = 128; // elements per LDS chunk
-constexpr int kElemVals = 20;
+constexpr int kLanes = 16;   // lanes over (species, Y) pairs, and slots over phi groups
+// LDS for the records of one stage (as many elements as fit, at least one): three
+// workgroups of 256 per CU also leave 160 KB / 3 each
+constexpr int kStageBytes = 40 * 1024;
 
-__global__ __launch_bounds__(kSpecBlock) void k_spectra(SpectraArgs a) {
-  __shared__ double sel[kChunk][kElemVals];
+// Launch shape of one (TS, TP) variant.
+struct SpecShape {
+  int nsy;    // (species, Y) pairs
+  int gpp;    // groups of TP phi bins per pT
+  int ntg;    // such groups in all
+  int npb;    // largest number of different pT in a workgroup's 16 slots
+  int nel;    // elements per stage
+  int nby;    // workgroups over the transverse groups
+};
+
+// e^x = m 2^k with |m - 1| < 0.42 (finite x; |x| > 1e6 is cut there, where the value
+// over- or underflows all the same; NaN stays NaN): k = round(x log2 e), then the
+// Taylor series of e^r, |r| <= ln2 / 2, to r^13 / 13! (remainder < 1e-17).
+__device__ __forceinline__ double split_exp(double x, int& k) {
+  x = x > 1e6 ? 1e6 : x;
+  x = x < -1e6 ? -1e6 : x;
+  const double kd = rint(x * 1.4426950408889634);
+  double r = fma(kd, -0.6931471805599453, x);
+  r = fma(kd, -2.3190468138462996e-17, r);
+  double p = 1.0 / 6227020800.0;
+  p = fma(p, r, 1.0 / 479001600.0);
+  p = fma(p, r, 1.0 / 39916800.0);
+  p = fma(p, r, 1.0 / 3628800.0);
+  p = fma(p, r, 1.0 / 362880.0);
+  p = fma(p, r, 1.0 / 40320.0);
+  p = fma(p, r, 1.0 / 5040.0);
+  p = fma(p, r, 1.0 / 720.0);
+  p = fma(p, r, 1.0 / 120.0);
+  p = fma(p, r, 1.0 / 24.0);
+  p = fma(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p, r, 1.0);
+  p = fma(p, r, 1.0);
+  k = (int)kd;
+  return p;
+}
+
+// 1 / x: the hardware estimate y, one third-order step y (1 + e + e^2) with e = 1 - x y,
+// and the fix-up instruction for x = 0, infinite or NaN (about one ulp; no division
+// sequence).
+__device__ __forceinline__ double recip(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, y, 1.0);
+  y = fma(y, fma(e, e, e), y);
+  return __builtin_amdgcn_div_fixup(y, x, 1.0);
+}
+
+// Three waves per SIMD (a TS = 3, TP = 6 thread fits without spills; without the
+// bound the compiler takes 200 registers and two waves: 10.1 -> 9.4 ms for TP = 8 on
+// the 41660-element surface below).
+template <int TS, int TP, bool DF>
+__global__ __launch_bounds__(kSpecBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_spectra(SpectraArgs a, SpecShape sh) {
+  constexpr int NS = kLanes * TS, NT = kLanes * TP;  // pairs and transverse bins covered
+  constexpr int NR = DF ? 3 : 2;                     // double2 values per record
+  extern __shared__ double2 smem[];
+  double2* const recA = smem;                             // [nel][NR][npb][NS]
+  double2* const recB = recA + sh.nel * NR * sh.npb * NS;  // [nel][NR][NT]
+  double* const shmT = (double*)(recB + sh.nel * NR * NT);  // [npb][NS]
+  double* const shY = shmT + sh.npb * NS;                  // [NS]
+  double* const shmu = shY + NS;                           // [NS]
+  double* const shpx = shmu + NS;                          // [NT]
+  double* const shpy = shpx + NT;                          // [NT]
   const gdouble* el = (const gdouble*)a.elements;
   const gdouble* tab = (const gdouble*)a.tables;
-  const int nchunk_phi = (a.nphi + kPhi - 1) / kPhi;
-  const long nthr = (long)a.ns * a.nY * a.npt * nchunk_phi;
-  const long b = (long)blockIdx.x * kSpecBlock + threadIdx.x;
-  const bool act = b < nthr;
-  const long bb = act ? b : 0;
-  const int ic = (int)(bb % nchunk_phi);
-  const int ip = (int)((bb / nchunk_phi) % a.npt);
-  const int iy = (int)((bb / ((long)nchunk_phi * a.npt)) % a.nY);
-  const int s = (int)(bb / ((long)nchunk_phi * a.npt * a.nY));
+  const int tid = threadIdx.x;
+  const int sy0 = (int)(blockIdx.x / sh.nby) * NS, tg0 = (int)(blockIdx.x % sh.nby) * kLanes;
+  const int ip0 = tg0 / sh.gpp;
   // tables: mass, dof, stat, mu (ns each), Y (nY), pT (npt), cos phi, sin phi (nphi each)
-  const double m = tab[s], sig = tab[2 * a.ns + s], mu = tab[3 * a.ns + s];
-  const double Y = tab[4 * a.ns + iy];
-  const double pt = tab[4 * a.ns + a.nY + ip];
-  const gdouble* cphi = tab + 4 * a.ns + a.nY + a.npt;
+  const gdouble* tpt = tab + 4 * a.ns + a.nY;
+  const gdouble* cphi = tpt + a.npt;
   const gdouble* sphi = cphi + a.nphi;
-  const double mT = sqrt(m * m + pt * pt);
-  double px[kPhi], py[kPhi], acc[kPhi];
-#pragma unroll
-  for (int q = 0; q < kPhi; ++q) {
-    const int iq = ic * kPhi + q;
+  for (int k = tid; k < sh.npb * NS; k += kSpecBlock) {
+    const int sy = min(sy0 + k % NS, sh.nsy - 1), ip = min(ip0 + k / NS, a.npt - 1);
+    const double m = tab[sy / a.nY], pt = tpt[ip];
+    shmT[k] = sqrt(m * m + pt * pt);
+  }
+  for (int k = tid; k < NS; k += kSpecBlock) {
+    const int sy = min(sy0 + k, sh.nsy - 1);
+    shY[k] = tab[4 * a.ns + sy % a.nY];
+    shmu[k] = tab[3 * a.ns + sy / a.nY];
+  }
+  for (int k = tid; k < NT; k += kSpecBlock) {
+    const int tg = min(tg0 + k / TP, sh.ntg - 1), iq = (tg % sh.gpp) * TP + k % TP;
     const bool ok = iq < a.nphi;
-    px[q] = ok ? pt * cphi[iq] : 0.0;
-    py[q] = ok ? pt * sphi[iq] : 0.0;
-    acc[q] = 0.0;
+    const double pt = tpt[tg / sh.gpp];
+    shpx[k] = ok ? pt * cphi[iq] : 0.0;
+    shpy[k] = ok ? pt * sphi[iq] : 0.0;
+  }
+  const int lane = tid % kLanes, slot = tid / kLanes;
+  const int tg = min(tg0 + slot, sh.ntg - 1);
+  const int pb = tg / sh.gpp - ip0;  // this thread's pT among the workgroup's
+  double sig[TS], acc[TS][TP];
+#pragma unroll
+  for (int t = 0; t < TS; ++t) {
+    sig[t] = tab[2 * a.ns + min(sy0 + lane + kLanes * t, sh.nsy - 1) / a.nY];
+#pragma unroll
+    for (int q = 0; q < TP; ++q) acc[t][q] = 0.0;
   }
   const double invT = 1.0 / a.T;
-  const bool with_df = a.eps_plus_P > 0.0;
-  const double dfc = with_df ? 1.0 / (2.0 * a.T * a.T * a.eps_plus_P) : 0.0;
+  const double dfc = DF ? 1.0 / (2.0 * a.T * a.T * a.eps_plus_P) : 0.0;
   // this workgroup's slice of the elements
   const long per = (a.n + gridDim.y - 1) / gridDim.y;
   const long e0 = (long)blockIdx.y * per;
   const long e1 = e0 + per < a.n ? e0 + per : a.n;
-  for (long c0 = e0; c0 < e1; c0 += kChunk) {
-    const int cn = (int)(e1 - c0 < kChunk ? e1 - c0 : kChunk);
+  for (long c0 = e0; c0 < e1; c0 += sh.nel) {
+    const int cn = (int)(e1 - c0 < sh.nel ? e1 - c0 : sh.nel);
     __syncthreads();
-    for (int k = threadIdx.x; k < cn * kElemVals; k += kSpecBlock) {
-      const int e = k / kElemVals, v = k % kElemVals;
-      // stored: tau, eta, dS (4), u~ (3), pi~ (10), spare
-      const int src = v == 0 ? 1 : (v == 1 ? 4 : v + 3);
-      sel[e][v] = v < 19 ? el[(c0 + e) * kSurfRec + src] : 0.0;
+    // longitudinal records: (e^{x_L}, p.dSigma), (p~^tau, p~^eta), (p~p~pi~, k_L)
+    for (int k = tid; k < cn * sh.npb * NS; k += kSpecBlock) {
+      const int e = k / (sh.npb * NS), r = k - e * (sh.npb * NS);
+      const gdouble* g = el + (c0 + e) * kSurfRec;
+      const double yrel = shY[r % NS] - g[4], ux = g[9], uy = g[10], ue = g[11];
+      const double ut = sqrt(1.0 + ux * ux + uy * uy + ue * ue);
+      int ke, kl;
+      const double ey = ldexp(split_exp(yrel, ke), ke), iey = recip(ey);
+      // sinh by its series where the exponentials cancel (|yrel| < 0.3: y^15 / 15! < 2e-20)
+      const double y2 = yrel * yrel;
+      double ss = fma(y2, 1.0 / 6227020800.0, 1.0 / 39916800.0);
+      ss = fma(y2, ss, 1.0 / 362880.0);
+      ss = fma(y2, ss, 1.0 / 5040.0);
+      ss = fma(y2, ss, 1.0 / 120.0);
+      ss = fma(y2, ss, 1.0 / 6.0);
+      const double sy = fabs(yrel) < 0.3 ? fma(yrel * y2, ss, yrel) : 0.5 * (ey - iey);
+      const double mT = shmT[r], p0 = mT * (0.5 * (ey + iey)), p3 = mT * sy;
+      const double eL = split_exp((p0 * ut - p3 * ue - shmu[r % NS]) * invT, kl);
+      double2* out = recA + (e * NR * sh.npb) * NS + r;
+      out[0] = double2{eL, p0 * g[5] + p3 / g[1] * g[8]};
+      if constexpr (DF) {
+        const double ppi = p0 * p0 * g[12] + p3 * p3 * g[21] - 2.0 * p0 * p3 * g[15];
+        out[sh.npb * NS] = double2{p0, p3};
+        out[2 * sh.npb * NS] = double2{ppi * dfc, __hiloint2double(0, kl)};
+      } else {
+        out[sh.npb * NS] = double2{__hiloint2double(0, kl), 0.0};
+      }
+    }
+    // transverse records: (e^{x_T}, p.dSigma), (the factors of p~^tau and p~^eta), (p~p~pi~, k_T)
+    for (int k = tid; k < cn * NT; k += kSpecBlock) {
+      const int e = k / NT, r = k - e * NT;
+      const gdouble* g = el + (c0 + e) * kSurfRec;
+      const double x = shpx[r], y = shpy[r];
+      int kt;
+      const double eT = split_exp(-(x * g[9] + y * g[10]) * invT, kt);
+      double2* out = recB + (e * NR) * NT + r;
+      out[0] = double2{eT, x * g[6] + y * g[7]};
+      if constexpr (DF) {
+        const double ppi = x * x * g[16] + y * y * g[19] + 2.0 * (x * y * g[17]);
+        out[NT] = double2{-2.0 * (x * g[13] + y * g[14]) * dfc, 2.0 * (x * g[18] + y * g[20]) * dfc};
+        out[2 * NT] = double2{ppi * dfc, __hiloint2double(0, kt)};
+      } else {
+        out[NT] = double2{__hiloint2double(0, kt), 0.0};
+      }
     }
     __syncthreads();
-    if (!act) continue;
     for (int e = 0; e < cn; ++e) {
-      const double tau = sel[e][0], eta = sel[e][1];
-      const double dS0 = sel[e][2], dS1 = sel[e][3], dS2 = sel[e][4], dS3 = sel[e][5];
-      const double ux = sel[e][6], uy = sel[e][7], ue = sel[e][8];
-      const double ut = sqrt(1.0 + ux * ux + uy * uy + ue * ue);
-      const double yrel = Y - eta;
-      const double p0 = mT * cosh(yrel), p3 = mT * sinh(yrel);
-      const double pdS_l = p0 * dS0 + p3 / tau * dS3;  // longitudinal part of p.dSigma
-      const double pu_l = p0 * ut - p3 * ue;
-      double pi00 = 0, pi01 = 0, pi02 = 0, pi03 = 0, pi11 = 0, pi12 = 0, pi13 = 0, pi22 = 0,
-             pi23 = 0, pi33 = 0;
-      if (with_df) {
-        pi00 = sel[e][9];
-        pi01 = sel[e][10];
-        pi02 = sel[e][11];
-        pi03 = sel[e][12];
-        pi11 = sel[e][13];
-        pi12 = sel[e][14];
-        pi13 = sel[e][15];
-        pi22 = sel[e][16];
-        pi23 = sel[e][17];
-        pi33 = sel[e][18];
+      const double2* A = recA + (e * NR * sh.npb + pb) * NS + lane;
+      const double2* B = recB + e * NR * NT + slot * TP;
+      double2 a0[TS], a1[TS], a2[TS];
+#pragma unroll
+      for (int t = 0; t < TS; ++t) {
+        a0[t] = A[kLanes * t];
+        a1[t] = A[sh.npb * NS + kLanes * t];
+        if constexpr (DF) a2[t] = A[2 * sh.npb * NS + kLanes * t];
       }
 #pragma unroll
-      for (int q = 0; q < kPhi; ++q) {
-        const double pdS = pdS_l + px[q] * dS1 + py[q] * dS2;
-        const double pu = pu_l - px[q] * ux - py[q] * uy;
-        const double f = 1.0 / (exp((pu - mu) * invT) + sig);
-        double w = 1.0;
-        if (with_df) {
-          // p~_a p~_b pi~^{ab} with p~_a = (p0, -px, -py, -p3)
-          const double x = px[q], y = py[q];
-          const double ppi = p0 * p0 * pi00 + x * x * pi11 + y * y * pi22 + p3 * p3 * pi33 +
-                             2.0 * (-p0 * x * pi01 - p0 * y * pi02 - p0 * p3 * pi03 + x * y * pi12 +
-                                    x * p3 * pi13 + y * p3 * pi23);
-          w = 1.0 + (1.0 - sig * f) * ppi * dfc;
+      for (int q = 0; q < TP; ++q) {
+        const double2 b0 = B[q], b1 = B[NT + q];
+        double2 b2 = {0.0, 0.0};
+        if constexpr (DF) b2 = B[2 * NT + q];
+        const int kb = __double2loint(DF ? b2.y : b1.x);
+#pragma unroll
+        for (int t = 0; t < TS; ++t) {
+          const int ka = __double2loint(DF ? a2[t].y : a1[t].x);
+          const double f = recip(ldexp(a0[t].x * b0.x, ka + kb) + sig[t]);
+          const double pdS = a0[t].y + b0.y;
+          if constexpr (DF) {
+            const double ppi = fma(a1[t].x, b1.x, fma(a1[t].y, b1.y, a2[t].x + b2.x));
+            const double w = fma(fma(-sig[t], f, 1.0), ppi, 1.0);
+            acc[t][q] = fma(pdS, f * w, acc[t][q]);
+          } else {
+            acc[t][q] = fma(pdS, f, acc[t][q]);
+          }
         }
-        acc[q] += pdS * f * w;
       }
     }
   }
-  if (!act) return;
+  if (tg0 + slot >= sh.ntg) return;
   gdouble* part = (gdouble*)a.partial + (long)blockIdx.y * a.nbins;
 #pragma unroll
-  for (int q = 0; q < kPhi; ++q) {
-    const int iq = ic * kPhi + q;
-    if (iq < a.nphi) part[(((long)s * a.nY + iy) * a.npt + ip) * a.nphi + iq] = acc[q];
+  for (int t = 0; t < TS; ++t) {
+    const int sy = sy0 + lane + kLanes * t;
+    if (sy >= sh.nsy) continue;
+#pragma unroll
+    for (int q = 0; q < TP; ++q) {
+      const int iq = (tg % sh.gpp) * TP + q;
+      if (iq < a.nphi) part[((long)sy * a.npt + tg / sh.gpp) * a.nphi + iq] = acc[t][q];
+    }
   }
 }
 
@@ -142,6 +257,7 @@ __global__ __launch_bounds__(kSpecBlock) void k_spectra_fold(SpectraArgs a, int 
   const gdouble* part = (const gdouble*)a.partial;
   const gdouble* tab = (const gdouble*)a.tables;
   double sum = 0.0;
+#pragma unroll 8
   for (int k = 0; k < nslice; ++k) sum += part[(long)k * a.nbins + bin];
   const int s = (int)(bin / ((long)a.nY * a.npt * a.nphi));
   const double pref = 1.0 / ((2.0 * M_PI * kHbarc) * (2.0 * M_PI * kHbarc) * (2.0 * M_PI * kHbarc));
@@ -150,16 +266,80 @@ __global__ __launch_bounds__(kSpecBlock) void k_spectra_fold(SpectraArgs a, int 
 
 }  // namespace
 
-int spectra_slices(long n) {
-  const long s = (n + 2 * kChunk - 1) / (2 * kChunk);  // at least two chunks per slice
-  return (int)(s < 1 ? 1 : (s > kMaxSlices ? kMaxSlices : s));
+int spectra_min_slices(long n) {
+  const long s = (n + 255) / 256;  // at least 256 elements per slice
+  return (int)(s < 1 ? 1 : (s > kMinSlicesCap ? kMinSlicesCap : s));
 }
 
-int launch_spectra(const SpectraArgs& a, hipStream_t s) {
-  const int nslice = spectra_slices(a.n);
-  const long nthr = (long)a.ns * a.nY * a.npt * ((a.nphi + kPhi - 1) / kPhi);
-  const long gx = (nthr + kSpecBlock - 1) / kSpecBlock;
-  hipLaunchKernelGGL(k_spectra, dim3((unsigned)gx, (unsigned)nslice), dim3(kSpecBlock), 0, s, a);
+// Few bins or few elements leave most of the chip without a workgroup: there, slices
+// down to 16 elements, until about 2048 workgroups of the largest tile (48 pairs x 96
+// transverse bins) are out.  568 elements on 88 x 18 x 1 bins: 3 slices 448 us a call,
+// 36 slices 58 us; 7596 elements on 5 x 16 x 20: 166 -> 91 us.
+int spectra_slices(long n, long nbins) {
+  const long wg = (nbins + 4607) / 4608;
+  const long more = std::min({(n + 15) / 16, 2048 / wg, (long)kMaxSlices});
+  return (int)std::max<long>(spectra_min_slices(n), more);
+}
+
+namespace {
+
+SpecShape spec_shape(const SpectraArgs& a, int TS, int TP, bool df, size_t* lds) {
+  const int NS = kLanes * TS, NT = kLanes * TP, NR = df ? 3 : 2;
+  SpecShape sh;
+  sh.nsy = a.ns * a.nY;
+  sh.gpp = (a.nphi + TP - 1) / TP;
+  sh.ntg = a.npt * sh.gpp;
+  sh.npb = std::min((kLanes - 2 + sh.gpp) / sh.gpp + 1, a.npt);
+  const size_t one = (size_t)NR * (sh.npb * NS + NT) * sizeof(double2);
+  sh.nel = (int)std::max<size_t>(1, std::min<size_t>(8, kStageBytes / one));
+  sh.nby = (sh.ntg + kLanes - 1) / kLanes;
+  *lds = sh.nel * one + (size_t)(sh.npb * NS + 2 * NS + 2 * NT) * sizeof(double);
+  return sh;
+}
+
+// Estimated instruction slots per element of a variant: bins of whole workgroups at 22
+// slots, or the LDS reads of the two record sets (8 clocks per 16 bytes a lane) where
+// those take longer, plus the records themselves (75 and 50 slots).
+double spec_cost(const SpectraArgs& a, int TS, int TP, bool df) {
+  size_t lds;
+  const SpecShape sh = spec_shape(a, TS, TP, df, &lds);
+  const double wg = (double)((sh.nsy + kLanes * TS - 1) / (kLanes * TS)) * sh.nby;
+  const double eval = std::max(22.0 * TS * TP, 8.0 * (df ? 3 : 2) * (TS + TP));
+  return wg * (kSpecBlock * eval + 75.0 * sh.npb * kLanes * TS + 50.0 * kLanes * TP);
+}
+
+template <int TS, int TP>
+void launch_variant(const SpectraArgs& a, int nslice, hipStream_t s) {
+  const bool df = a.eps_plus_P > 0.0;
+  size_t lds;
+  const SpecShape sh = spec_shape(a, TS, TP, df, &lds);
+  const dim3 grid((unsigned)((sh.nsy + kLanes * TS - 1) / (kLanes * TS)) * sh.nby, (unsigned)nslice);
+  if (df)
+    hipLaunchKernelGGL((k_spectra<TS, TP, true>), grid, dim3(kSpecBlock), lds, s, a, sh);
+  else
+    hipLaunchKernelGGL((k_spectra<TS, TP, false>), grid, dim3(kSpecBlock), lds, s, a, sh);
+}
+
+}  // namespace
+
+int launch_spectra(const SpectraArgs& a, int nslice, hipStream_t s) {
+  // the variant with the fewest estimated slots: the larger tiles share more, the
+  // smaller ones pad less where there are few pairs or phi bins
+  static const struct {
+    int ts, tp;
+    void (*fn)(const SpectraArgs&, int, hipStream_t);
+  } kVar[] = {{3, 6, launch_variant<3, 6>}, {3, 4, launch_variant<3, 4>}, {3, 1, launch_variant<3, 1>},
+              {1, 6, launch_variant<1, 6>}, {1, 4, launch_variant<1, 4>}, {1, 1, launch_variant<1, 1>}};
+  int best = 0;
+  double cost = 1e300;
+  for (int v = 0; v < (int)(sizeof(kVar) / sizeof(kVar[0])); ++v) {
+    const double c = spec_cost(a, kVar[v].ts, kVar[v].tp, a.eps_plus_P > 0.0);
+    if (c < cost) {
+      cost = c;
+      best = v;
+    }
+  }
+  kVar[best].fn(a, nslice, s);
   const long fx = (a.nbins + kSpecBlock - 1) / kSpecBlock;
   hipLaunchKernelGGL(k_spectra_fold, dim3((unsigned)fx), dim3(kSpecBlock), 0, s, a, nslice);
   return hipGetLastError() == hipSuccess ? 0 : -1;
@@ -181,7 +361,7 @@ extern "C" {
 size_t ktmi_spectra_workspace_bytes(long n, int ns, int nY, int npt, int nphi) {
   if (n < 0 || ns < 1 || nY < 1 || npt < 1 || nphi < 1) return 0;
   const size_t nbins = (size_t)ns * nY * npt * nphi;
-  return (spectra_table_doubles(ns, nY, npt, nphi) + (size_t)spectra_slices(n) * nbins) *
+  return (spectra_table_doubles(ns, nY, npt, nphi) + (size_t)spectra_slices(n, (long)nbins) * nbins) *
          sizeof(double);
 }
 
@@ -192,10 +372,16 @@ int ktmi_spectra(const double* elements, long n, double T, double eps_plus_P, in
   if (n < 0 || (n > 0 && !elements) || !(T > 0) || !(eps_plus_P >= 0) || ns < 1 || nY < 1 ||
       npt < 1 || nphi < 1 || !mass || !dof || !stat || !mu || !Y || !pt || !phi || !out || !ws)
     return KTMI_EINVAL;
-  if (ws_bytes < ktmi_spectra_workspace_bytes(n, ns, nY, npt, nphi)) return KTMI_EINVAL;
+  // as many slices as the workspace holds, up to what ktmi_spectra_workspace_bytes asks
+  // for; the fewest the call takes are those of spectra_min_slices
+  const size_t ntab = spectra_table_doubles(ns, nY, npt, nphi);
+  const size_t nbins = (size_t)ns * nY * npt * nphi, room = ws_bytes / sizeof(double);
+  const size_t fit = room < ntab ? 0 : (room - ntab) / nbins;
+  if (fit < (size_t)spectra_min_slices(n)) return KTMI_EINVAL;
+  const int nslice = (int)std::min<size_t>(fit, (size_t)spectra_slices(n, (long)nbins));
   for (int s = 0; s < ns; ++s)
     if (!(mass[s] >= 0) || stat[s] < -1 || stat[s] > 1) return KTMI_EINVAL;
-  std::vector<double> tab(spectra_table_doubles(ns, nY, npt, nphi), 0.0);
+  std::vector<double> tab(ntab, 0.0);
   for (int s = 0; s < ns; ++s) {
     tab[s] = mass[s];
     tab[ns + s] = dof[s];
@@ -224,11 +410,11 @@ int ktmi_spectra(const double* elements, long n, double T, double eps_plus_P, in
   a.nY = nY;
   a.npt = npt;
   a.nphi = nphi;
-  a.nbins = (long)ns * nY * npt * nphi;
+  a.nbins = (long)nbins;
   a.tables = dtab;
   a.partial = dtab + tab.size();
   a.out = out;
-  return launch_spectra(a, st) == 0 ? KTMI_OK : KTMI_EHIP;
+  return launch_spectra(a, nslice, st) == 0 ? KTMI_OK : KTMI_EHIP;
 }
 
 }  // extern "C"

@@ -8,7 +8,9 @@
 
 namespace ktmi {
 
-constexpr int kMaxSlices = 64;  // element slices summed by the fold kernel
+// element slices summed by the fold kernel: at least 256 elements each up to
+// kMinSlicesCap slices, and more where that leaves the chip idle
+constexpr int kMinSlicesCap = 64, kMaxSlices = 512;
 
 struct SpectraArgs {
   const double* elements;  // n surface records of kSurfRec doubles
@@ -17,11 +19,12 @@ struct SpectraArgs {
   int ns, nY, npt, nphi;
   long nbins;              // ns nY npt nphi
   const double* tables;    // mass, dof, stat, mu (ns each), Y, pT, cos phi, sin phi
-  double* partial;         // spectra_slices(n) x nbins
+  double* partial;         // slices x nbins
   double* out;             // nbins
 };
 
-int spectra_slices(long n);
-int launch_spectra(const SpectraArgs& a, hipStream_t s);
+int spectra_min_slices(long n);           // fewest slices a call runs with
+int spectra_slices(long n, long nbins);  // slices a workspace of the asked size holds
+int launch_spectra(const SpectraArgs& a, int nslice, hipStream_t s);
 
 }  // namespace ktmi

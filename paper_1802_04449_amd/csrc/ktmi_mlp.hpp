@@ -88,11 +88,10 @@ __device__ __forceinline__ float mlp_z_fp32(const float* __restrict__ prm, const
 // D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32] in accumulator register r.  A lane
 // needs half of its B slice from its own sample and half from the sample of
 // lane l ^ 32, exchanged with one cross-half shuffle per 32-bit pair; no LDS.
-// w2bf: W2 as BF16 (row-major).  h2 (optional) receives the lane's own hidden
-// outputs.
+// w2bf: W2 as BF16 (row-major).
 __device__ __forceinline__ float mlp_z_mfma(const float* __restrict__ prm,
                                             const uint16_t* __restrict__ w2bf,
-                                            const float h1[kMlpH], float* h2 = nullptr) {
+                                            const float h1[kMlpH]) {
   const int l = threadIdx.x & 63;
   const bool upper = l >= 32;
   const int row = l & 31;
@@ -136,15 +135,6 @@ __device__ __forceinline__ float mlp_z_mfma(const float* __restrict__ prm,
     send += prm[kOW3 + i] * other[r];
   }
   const float z = prm[kOB3] + keep + __shfl_xor(send, 32, 64);
-  if (h2) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float got = __shfl_xor(other[r], 32, 64);  // partner's rows of this lane's sample
-      const int lo_i = 8 * (r >> 2) + (r & 3);
-      h2[lo_i] = upper ? got : mine[r];
-      h2[lo_i + 4] = upper ? mine[r] : got;
-    }
-  }
   return z;
 }
 

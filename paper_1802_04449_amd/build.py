@@ -24,6 +24,10 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I" + os.path.join(ROOT, "include"),
 ]
+# FP64 stencil passes: products and sums are fused where the source writes them in one
+# expression and nowhere else, so every instance of a pass (tile shapes, the small-event
+# kernels, grouped launches) rounds alike and their fields are equal bit for bit
+FP64_FLAGS = ["-ffp-contract=on"]
 NUM_PASSES = 11  # first estimate, stage1 (viscous, ideal), stage2 pi, stage2 T (viscous, ideal),
 #                 stage1 viscous and stage2 pi with the lambda_1 term, stage1 / stage2 pi /
 #                 stage2 T with bulk pressure and baryon density
@@ -38,7 +42,8 @@ def _jobs():
         for rt, tag in (("double", "f64"), ("float", "f32")):
             jobs.append((f"stencil_p{p}_{tag}", os.path.join(CSRC, "ktmi_stencil.hip"),
                          [f"-DKTMI_PASS={p}", f"-DKTMI_RT={rt}",
-                          f"-DKTMI_LAUNCH_FN=launch_pass{p}_{tag}"]))
+                          f"-DKTMI_LAUNCH_FN=launch_pass{p}_{tag}"] +
+                         (FP64_FLAGS if rt == "double" else [])))
     return jobs
 
 

@@ -199,6 +199,7 @@ struct ktmi_handle {
   long step = 0;
   int nblk = 0;      // blocks of the flat (per-cell) kernels
   int tile = 0;      // index into kTiles
+  bool tile_auto = true;  // tile chosen by the library: small events take kSmallTiles
   TileGrid tg{};     // tile grid of the stencil kernels
   size_t fstride = 0;
   bool timing = false;
@@ -321,14 +322,15 @@ static bool desc_ok(const ktmi_desc* d, std::string* why) {
   return true;
 }
 
-static TileGrid tile_grid(const ktmi_desc* d, int t) {
+static TileGrid tile_grid(const ktmi_desc* d, const TileShape& t) {
   TileGrid g;
-  g.ntx = (d->nx + kTiles[t].tx - 1) / kTiles[t].tx;
-  g.nty = (d->ny + kTiles[t].ty - 1) / kTiles[t].ty;
-  g.ntz = (d->ne + kTiles[t].tz - 1) / kTiles[t].tz;
+  g.ntx = (d->nx + t.tx - 1) / t.tx;
+  g.nty = (d->ny + t.ty - 1) / t.ty;
+  g.ntz = (d->ne + t.tz - 1) / t.tz;
   g.ntiles = g.ntx * g.nty * g.ntz;
   return g;
 }
+static TileGrid tile_grid(const ktmi_desc* d, int t) { return tile_grid(d, kTiles[t]); }
 
 // Default tile: fewest padded thread slots, counting double for shapes whose eta
 // extent is shorter than min(ne, 16) (their lanes stride across eta rows, so
@@ -348,10 +350,42 @@ static int auto_tile(const ktmi_desc* d) {
   return best;
 }
 
+// Small events: up to 1024 tiles of the automatic shape (2048 on one eta cell, where the
+// shape's vacuum test spares less), and up to 3072 where that shape pads the grid more
+// than the small tiles do (64 thread slots each).
+static int small_tile(const ktmi_desc* d) { return d->ne > 1 ? 0 : 1; }
+static bool small_event(const ktmi_desc* d) {
+  const int n = tile_grid(d, auto_tile(d)).ntiles;
+  if (n <= (d->ne > 1 ? 1024 : 2048)) return true;
+  return n <= 3072 && 64.0 * tile_grid(d, kSmallTiles[small_tile(d)]).ntiles <= (double)n * kBlock;
+}
+
 static int max_tiles(const ktmi_desc* d) {
   int m = 0;
   for (int t = 0; t < kNumTiles; ++t) m = std::max(m, tile_grid(d, t).ntiles);
+  if (small_event(d)) m = std::max(m, tile_grid(d, kSmallTiles[small_tile(d)]).ntiles);
   return m;
+}
+
+// Tile index and tile grid of a handle's launches: the small-event kernels (bitwise the
+// same fields) for a small event whose tile the library chose, in FP64 (in FP32 the two
+// kernels' products are fused differently and the results move by 1e-9) and without the
+// network.  Alone or in a group alike: the diagnostic sums then have the same order.
+// Measured in us per viscous step, large-grid kernels -> small-event ones, by the number
+// of tiles: 100 (151x151x1 hotspots) 84 -> 47, 361 (301x301x1) 88 -> 57, 512 (64x64x17
+// without vacuum) 122 -> 88, 1444 (601x601x1 hotspots) 189 -> 134, 2048 and 2700 of padded
+// grids (128x128x17, 120x120x33, without vacuum) 310 -> 252 and 411 -> 391; but 1575 of an
+// unpadded one (60x60x105, without vacuum) 291 -> 304, 3250 (101x99x65) 515 -> 555, and on
+// the 201x201x105 event, most of whose tiles are vacuum and skip their face rounds as a
+// whole in the large-grid kernels, 1200 -> 1700.
+static int run_tile(const ktmi_handle* h, TileGrid* tg) {
+  *tg = h->tg;
+  if (!h->tile_auto || h->d.precision != KTMI_FP64 || h->d.guess == KTMI_GUESS_MLP ||
+      !small_event(&h->d))
+    return h->tile;
+  const int id = small_tile(&h->d);
+  *tg = tile_grid(&h->d, kSmallTiles[id]);
+  return kNumTiles + id;
 }
 
 // Doubles reserved for the per-tile flags: 4 ints per tile of the largest grid
@@ -408,7 +442,10 @@ static StepParams step_params(const ktmi_handle* h) {
   p.newton_maxit = h->d.newton_maxit;
   p.vac_zero = h->d.pi_reg > 0.0 && h->p_at0 == 0.0;
   // quiet tiles: neighbourhood radius in tiles covering 6 cells per axis
-  const int td[3] = {kTiles[h->tile].tx, kTiles[h->tile].ty, kTiles[h->tile].tz};
+  TileGrid tg;
+  const int rt = run_tile(h, &tg);
+  const TileShape& ts = rt < kNumTiles ? kTiles[rt] : kSmallTiles[rt - kNumTiles];
+  const int td[3] = {ts.tx, ts.ty, ts.tz};
   for (int a = 0; a < 3; ++a) p.quiet_r[a] = h->quiet_on ? (6 + td[a] - 1) / td[a] : 0;
   p.guess = h->d.guess;
   p.mlp_mfma = h->mlp_mode == KTMI_MLP_BF16;
@@ -467,12 +504,12 @@ static void launch_class(int pass, hipStream_t s, int tile, int precision, bool 
   kPassLaunch[pass][precision == KTMI_MIXED ? 1 : 0](s, tile, net, evs, gt);
 }
 
-static GroupTable single_table(const ktmi_handle* h) {
+static GroupTable single_table(const TileGrid& tg) {
   GroupTable gt;
   memset(&gt, 0, sizeof(gt));
   gt.nev = 1;
   gt.start[0] = 0;
-  gt.start[1] = h->tg.ntiles;
+  gt.start[1] = tg.ntiles;
   return gt;
 }
 
@@ -482,7 +519,7 @@ static EventDesc make_event(const ktmi_handle* h) {
   ev.f = h->f;
   ev.p = step_params(h);
   ev.eos = h->eos;
-  ev.tg = h->tg;
+  (void)run_tile(h, &ev.tg);
   ev.cart = h->d.cartesian;
   ev.viscous = h->d.viscous;
   ev.clock = h->clock;
@@ -539,9 +576,10 @@ static int step_mode(const ktmi_handle* h) {
 }
 
 static int enqueue_step(ktmi_handle* h) {
-  const GroupTable gt = single_table(h);
-  int rc = enqueue_class_step(h, h->stream, h->tile, h->d.precision, step_mode(h), uses_net(h),
-                              h->dev_ev, gt);
+  TileGrid tg;
+  const int tile = run_tile(h, &tg);
+  int rc = enqueue_class_step(h, h->stream, tile, h->d.precision, step_mode(h), uses_net(h),
+                              h->dev_ev, single_table(tg));
   if (rc) return rc;
   return launch(h, K_REDUCE, [&] {
     hipLaunchKernelGGL(k_reduce, dim3(kNP), dim3(kRedBlock), 0, h->stream, h->dev_ev);
@@ -561,9 +599,10 @@ static int clear_quiet(ktmi_handle* h) {
 static int finish_initial(ktmi_handle* h) {
   if (int rc = upload_event(h)) return rc;
   hipLaunchKernelGGL(k_set_clock, dim3(1), dim3(64), 0, h->stream, h->clock, h->tau);
-  const GroupTable gt = single_table(h);
+  TileGrid tg;
+  const int tile = run_tile(h, &tg);
   int rc = launch(h, K_FIRST, [&] {
-    launch_class(PASS_FIRST, h->stream, h->tile, h->d.precision, false, h->dev_ev, gt);
+    launch_class(PASS_FIRST, h->stream, tile, h->d.precision, false, h->dev_ev, single_table(tg));
   });
   if (rc) return rc;
   rc = launch(h, K_INIT, [&] {
@@ -678,7 +717,8 @@ int ktmi_create(const ktmi_desc* d, ktmi_handle** out) {
   h->d = *d;
   h->tau = d->tau0;
   h->nblk = num_blocks(d);
-  h->tile = d->tile < 0 ? auto_tile(d) : d->tile;
+  h->tile_auto = d->tile < 0;
+  h->tile = h->tile_auto ? auto_tile(d) : d->tile;
   h->tg = tile_grid(d, h->tile);
   h->fstride = field_stride(d);
   h->eos.kind = 0;
@@ -956,9 +996,12 @@ int ktmi_set_guess(ktmi_handle* h, int guess) {
     return fail(h, KTMI_EINVAL, "unknown guess mode");
   if (guess == KTMI_GUESS_MLP && !h->mlp_ok)
     return fail(h, KTMI_ESTATE, "guess mode KTMI_GUESS_MLP needs ktmi_set_mlp first");
+  TileGrid tg;
+  const int before = run_tile(h, &tg);
   h->d.guess = guess;
   h->ev_dirty = true;
-  return KTMI_OK;
+  // the network's instances keep the large-grid tiles: the flags are per tile
+  return run_tile(h, &tg) == before ? KTMI_OK : clear_quiet(h);
 }
 
 int ktmi_harvest(ktmi_handle* h, double* E, double* M, double* eps) {
@@ -1146,7 +1189,8 @@ int ktmi_get_tile(const ktmi_handle* h) { return h ? h->tile : KTMI_EINVAL; }
 int ktmi_set_tile(ktmi_handle* h, int t) {
   if (!h) return KTMI_EINVAL;
   if (t < -1 || t >= kNumTiles) return fail(h, KTMI_EINVAL, "tile index out of range");
-  h->tile = t < 0 ? auto_tile(&h->d) : t;
+  h->tile_auto = t < 0;
+  h->tile = h->tile_auto ? auto_tile(&h->d) : t;
   h->tg = tile_grid(&h->d, h->tile);
   h->ev_dirty = true;
   return clear_quiet(h);  // flags are per tile of the old shape
@@ -1155,7 +1199,9 @@ int ktmi_set_tile(ktmi_handle* h, int t) {
 int ktmi_quiet_tiles(ktmi_handle* h, long* quiet, long* total) {
   if (!h || !quiet || !total) return KTMI_EINVAL;
   if (!h->ready) return fail(h, KTMI_ESTATE, "no state");
-  const int nt = h->tg.ntiles;
+  TileGrid tg;
+  (void)run_tile(h, &tg);
+  const int nt = tg.ntiles;
   std::vector<int> flags(nt);
   // the step with clock parity p writes flag buffer 1 - p: after an odd number
   // of steps the latest flags are in buffer 1
@@ -1204,16 +1250,18 @@ int ktmi_group_create(ktmi_handle* const* hs, int nev, void* ws, size_t bytes, k
   // classes in first-seen order; events keep their order inside a class
   std::vector<int> order;
   std::vector<std::vector<int>> members;
+  TileGrid tg;
   for (int i = 0; i < nev; ++i) {
     const ktmi_handle* h = hs[i];
+    const int tile = run_tile(h, &tg);
     int c = -1;
     for (size_t k = 0; k < g->classes.size(); ++k)
-      if (g->classes[k].tile == h->tile && g->classes[k].precision == h->d.precision &&
+      if (g->classes[k].tile == tile && g->classes[k].precision == h->d.precision &&
           g->classes[k].mode == step_mode(h) && g->classes[k].net == uses_net(h))
         c = (int)k;
     if (c < 0) {
       ktmi_group::Class cl{};
-      cl.tile = h->tile;
+      cl.tile = tile;
       cl.precision = h->d.precision;
       cl.mode = step_mode(h);
       cl.net = uses_net(h);
@@ -1236,8 +1284,9 @@ int ktmi_group_create(ktmi_handle* const* hs, int nev, void* ws, size_t bytes, k
     int t = 0;
     for (int m = 0; m < cl.gt.nev; ++m) {
       ktmi_handle* h = hs[members[k][m]];
+      (void)run_tile(h, &tg);
       cl.gt.start[m] = t;
-      t += h->tg.ntiles;
+      t += tg.ntiles;
       g->hs.push_back(h);
       g->host.push_back(make_event(h));
       pos++;

@@ -23,9 +23,6 @@
 #ifndef KTMI_PI1_SPARSE
 #define KTMI_PI1_SPARSE 1
 #endif
-#ifndef KTMI_S2PI_STREAM
-#define KTMI_S2PI_STREAM 1
-#endif
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -282,14 +279,13 @@ __device__ __forceinline__ Ctx load_ctx(const EventDesc* __restrict__ evs, const
 }
 
 template <int TX, int TY, int TZ>
-__device__ __forceinline__ Pos cell_pos(const StepParams& p, const TileGrid& tg, int t) {
+__device__ __forceinline__ Pos cell_pos(const StepParams& p, const TileGrid& tg, int t, int tid) {
   Pos q;
   const int tk = t % tg.ntz, r = t / tg.ntz;
   const int tj = r % tg.nty, ti = r / tg.nty;
   q.i0 = ti * TX;
   q.j0 = tj * TY;
   q.k0 = tk * TZ;
-  const int tid = threadIdx.x;
   q.lz = tid % TZ;
   q.ly = (tid / TZ) % TY;
   q.lx = tid / (TZ * TY);
@@ -530,126 +526,6 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
   return c;
 }
 
-// KT face flux H = [F(Q^r) + F(Q^l)]/2 - c (Q^r - Q^l)/2 (Sec. III, eq. flux_out)
-// at the face between cells a and a+1 along `axis` (1 = x, 2 = y, 3 = eta).
-// `base` is the flat index of the row's cell with coordinate 0 along the axis.
-// Components 0..3: T~^{d nu} part (if DO_T); 4..13: u~^d pi~ part (if DO_PI);
-// BK: 14, 15 the u~^d Pi and u~^d n parts (Pi also adds to P in T~'s part).
-// Returns the face's local speed c.  A face whose four stencil cells are exact
-// vacuum (all primitives zero) has H = 0 and c = c_vac, so it skips the arithmetic.
-// R is the arithmetic type (double, or float on the mixed-precision path).
-template <typename R, bool DO_T, bool DO_PI, int PI_SRC, bool BK = false>
-__device__ __forceinline__ R face_flux_all(const GField& e, const FSet& u,
-                                       const FSet& pi, int base, int a, int n,
-                                       int stride, int axis, R tauf, const StepParams& p,
-                                       const EosDev& eos, R* out, int F) {
-  int idx[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) idx[t] = base + clampi(a - 1 + t, 0, n - 1) * stride;
-  // Vacuum faces skip all arithmetic.  Every state the kernels write has u~ = 0
-  // where e = 0 (the root solve and the cutoff return all-zero primitives), and
-  // with PI_SRC 0/1 pi~ reads as zero there too, so e alone decides: it is
-  // loaded first and a vacuum face skips the other loads.  As-stored pi~
-  // (PI_SRC 2) can be nonzero where e = 0, so there the whole stencil is loaded
-  // at once (no dependent second round of loads) and e and pi~ decide.
-  constexpr int NQ = BK ? 12 : 10, NC = 4 + NQ;
-  double ev[4];
-  bool vac = true;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    ev[t] = e[idx[t]];
-    vac = vac && (ev[t] == 0.0);
-  }
-  R q4[NC][4];
-  if (PI_SRC == 2) {
-    // Without the pi~ flux only the components in T~'s density (tau nu) and
-    // flux (axis nu) matter (and Pi): the others are neither loaded nor tested.
-#pragma unroll
-    for (int m = 0; m < NQ; ++m) {
-      const bool used = DO_PI || m < 4 || m == sym(axis, 1) || m == sym(axis, 2) ||
-                        m == sym(axis, 3) || m == 10;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const double x = used ? ldq<R>(pi[m], idx[t]) : 0.0;
-        vac = vac && (x == 0.0);
-        q4[4 + m][t] = (R)x;
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) q4[1 + m][t] = (R)u[m][idx[t]];
-  }
-  if (vac) {  // only the components the pass uses: the LDS holds no others
-#pragma unroll
-    for (int k = 0; k < NC; ++k)
-      if (k < 4 ? DO_T : DO_PI) out[k * F] = R(0);
-    return (R)p.c_vac;
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) q4[0][t] = (R)ev[t];
-  if (PI_SRC != 2) {
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) q4[1 + m][t] = (R)u[m][idx[t]];
-#pragma unroll
-    for (int m = 0; m < NQ; ++m)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) q4[4 + m][t] = (R)ld_pi<PI_SRC, R>(pi, m, idx[t], ev[t]);
-  }
-  R qL[NC], qR[NC];
-  const R th = (R)p.theta;
-#pragma unroll
-  for (int v = 0; v < NC; ++v) {
-    const R a0 = q4[v][0], a1 = q4[v][1], a2 = q4[v][2], a3 = q4[v][3];
-    qL[v] = a1 + R(0.5) * mm_slope_r<R>(th, a0, a1, a2);
-    qR[v] = a2 - R(0.5) * mm_slope_r<R>(th, a1, a2, a3);
-  }
-  // Scalars of the two states first (u~^tau, P, c_s^2, e + P, speed), then each
-  // flux component from them and the face states, straight to LDS: only the
-  // face states stay live, not the Q and F arrays of both sides.
-  R ut[2], P[2], w[2], ud[2], sp[2];
-#pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    const R* q = side ? qR : qL;
-    const R ux = q[1], uy = q[2], ue = q[3];
-    ut[side] = sqrt(R(1) + ux * ux + uy * uy + ue * ue);
-    R cs2;
-    eos_p_cs2_r<R>(eos, q[0], P[side], cs2);
-    if constexpr (BK) P[side] = P[side] + q[14];  // P + Pi
-    w[side] = (q[0] > R(0) ? q[0] : R(0)) + P[side];
-    const R u4[4] = {ut[side], ux, uy, ue};
-    ud[side] = u4[axis];
-    sp[side] = local_speed_r<R>(ut[side], ux, uy, ue, ud[side], cs2);
-  }
-  const R c = fmax(sp[0], sp[1]);
-  if (DO_T) {
-#pragma unroll
-    for (int nu = 0; nu < 4; ++nu) {
-      R Q[2], Fx[2];
-#pragma unroll
-      for (int side = 0; side < 2; ++side) {
-        const R* q = side ? qR : qL;
-        const R un = nu == 0 ? ut[side] : q[nu];
-        Q[side] = tauf * (w[side] * ut[side] * un - (nu == 0 ? P[side] : R(0)) + q[4 + sym(0, nu)]);
-        Fx[side] =
-            tauf * (w[side] * ud[side] * un + (nu == axis ? P[side] : R(0)) + q[4 + sym(axis, nu)]);
-      }
-      out[nu * F] = R(0.5) * (Fx[0] + Fx[1]) - R(0.5) * c * (Q[1] - Q[0]);
-    }
-  }
-#pragma unroll
-  for (int m = 0; m < NQ; ++m) {
-    if (DO_PI) {
-      const R QL = ut[0] * qL[4 + m], QR = ut[1] * qR[4 + m];
-      const R FL = ud[0] * qL[4 + m], FR = ud[1] * qR[4 + m];
-      out[(4 + m) * F] = R(0.5) * (FL + FR) - R(0.5) * c * (QR - QL);
-    }
-  }
-  return c;
-}
-
 // Faces of a TX x TY x TZ tile along each axis, F_d = (T_d + 1) N / T_d, split
 // into M_d = kBlock floor(F_d / kBlock) faces evaluated in full rounds (one face
 // per thread and round) and R_d = F_d - M_d remainder faces.  The remainders of
@@ -708,15 +584,8 @@ __device__ __forceinline__ double eval_face(const GField& e, const FSet& u,
   if (inrow && ga <= nd) {
     const int base = d == 0 ? (gj * p.ne + gk)
                             : (d == 1 ? (gi * p.ny) * p.ne + gk : (gi * p.ny + gj) * p.ne);
-    // stage 1 (pi~ masked by e): the streamed evaluation (fewer registers);
-    // stage 2 (as-stored pi~): all loads at once with the per-face e/pi~ test
-    RT c;
-    if constexpr (PI_SRC == 2 && DO_PI && !KTMI_S2PI_STREAM)
-      c = face_flux_all<RT, DO_T, DO_PI, PI_SRC, BK>(e, u, pi, base, ga - 1, nd, stride, d + 1,
-                                                     (RT)tauf, p, eos, out, S);
-    else
-      c = face_flux_stream<RT, DO_T, DO_PI, PI_SRC, BK>(e, u, pi, base, ga - 1, nd, stride, d + 1,
-                                                        (RT)tauf, p, eos, out, S, ez);
+    const RT c = face_flux_stream<RT, DO_T, DO_PI, PI_SRC, BK>(
+        e, u, pi, base, ga - 1, nd, stride, d + 1, (RT)tauf, p, eos, out, S, ez);
     return (double)c * inv_del;
   }
 #pragma unroll
@@ -927,14 +796,8 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
         if (inrow && ga <= nd) {
           const int base = d == 0 ? (gj * p.ne + gk)
                                   : (d == 1 ? (gi * p.ny) * p.ne + gk : (gi * p.ny + gj) * p.ne);
-          RT c;
-          if constexpr (PI_SRC == 2 && DO_PI && !KTMI_S2PI_STREAM)
-            c = face_flux_all<RT, DO_T, DO_PI, PI_SRC, BK>(e, u, pi, base, ga - 1, nd, stride, d + 1,
-                                                           (RT)tauf, p, eos, lds + f, F);
-          else
-            c = face_flux_stream<RT, DO_T, DO_PI, PI_SRC, BK>(e, u, pi, base, ga - 1, nd, stride,
-                                                              d + 1, (RT)tauf, p, eos, lds + f, F,
-                                                              ez);
+          const RT c = face_flux_stream<RT, DO_T, DO_PI, PI_SRC, BK>(
+              e, u, pi, base, ga - 1, nd, stride, d + 1, (RT)tauf, p, eos, lds + f, F, ez);
           cfl = fmax(cfl, (double)c * inv_del);
         } else {
   #pragma unroll
@@ -1179,20 +1042,87 @@ __device__ __forceinline__ void regulate(const EosDev& eos, const StepParams& p,
 }
 
 // ---------------------------------------------------------------------------
-// Workgroup reduction of the diagnostic partials (wave64 shuffles, then LDS).
+// Workgroup reduction of the diagnostic partials.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void block_partials(double v[kNP], gdouble* out, int ntiles, int tile) {
+
+// One thread's contribution: geometric source, c h / Delta, sum and maximum terms, the
+// root solve's iterations and flags (kVacAfter: e = 0 after the step).
+struct CellDiag {
+  double geo = 0.0, cfl = 0.0, tsum = 0.0, emax = 0.0;
+  int it = 0, fl = 0;
+};
+constexpr int kVacAfter = 64;
+
+__device__ __forceinline__ void count_solve(CellDiag& d, int it, int fl) {
+  d.it = it;
+  d.fl |= it == 0 ? fl & (kNan | kNeg) : fl;  // it = 0: decided before iterating
+}
+
+// x of the lane that the DPP control selects (all lanes active).
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  return __hiloint2double(dpp<CTRL>(__double2hiint(x)), dpp<CTRL>(__double2loint(x)));
+}
+__device__ __forceinline__ int lane_of(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
+__device__ __forceinline__ double lane_of(double x, int l) {
+  return __hiloint2double(lane_of(__double2hiint(x), l), lane_of(__double2loint(x), l));
+}
+
+// Fold of a wave with op: inside each row of 16 lanes by the neighbour at distance 1, 2,
+// then the mirrored half row and row, then the four rows in a fixed order.
+template <typename T, typename OP>
+__device__ __forceinline__ T wave_fold(T x, OP op) {
+  x = op(x, dpp<0xB1>(x));   // lanes 1 0 3 2 of each four
+  x = op(x, dpp<0x4E>(x));   // lanes 2 3 0 1
+  x = op(x, dpp<0x141>(x));  // mirrored half row
+  x = op(x, dpp<0x140>(x));  // mirrored row
+  return op(op(lane_of(x, 0), lane_of(x, 16)), op(lane_of(x, 32), lane_of(x, 48)));
+}
+
+// A wave's partials.  Counters are counted by ballot, and a sum or maximum whose terms are
+// all zero (the waves of vacuum tiles, most of a heavy-ion grid) is not folded at all: 13
+// double shuffle folds per wave, as before, were a tenth of the average wave's
+// instructions (201x201x105 hotspot event, 10 steps: 13.15 -> 12.31 ms).
+__device__ __forceinline__ void wave_partials(const CellDiag& d, double v[kNP]) {
+  auto sum = [](auto a, auto b) { return a + b; };
+  auto mx = [](double a, double b) { return fmax(a, b); };
+  auto imx = [](int a, int b) { return a > b ? a : b; };
+  auto count = [&](bool c) { return (double)__popcll(__ballot(c)); };
+#pragma unroll
+  for (int s = 0; s < kNP; ++s) v[s] = 0.0;
+  if (__ballot(d.geo != 0.0)) v[P_GEO] = wave_fold(d.geo, sum);
+  if (__ballot(d.tsum != 0.0)) v[P_TSUM] = wave_fold(d.tsum, sum);
+  if (__ballot(d.emax != 0.0)) v[P_EMAX] = wave_fold(d.emax, mx);
+  v[P_CFL] = wave_fold(d.cfl, mx);
+  if (__ballot(d.it > 0)) {
+    v[P_SOLVES] = count(d.it > 0);
+    v[P_ITSUM] = (double)wave_fold(d.it, sum);
+    v[P_ITMAX] = (double)wave_fold(d.it, imx);
+  }
+  if (__ballot(d.fl != 0)) {
+    v[P_FALLBACK] = count(d.fl & kFallback);
+    v[P_NONCONV] = count(d.fl & kNonconv);
+    v[P_NAN] = count(d.fl & kNan);
+    v[P_CLAMP] = count(d.fl & kClamp);
+    v[P_VAC] = count(d.fl & kVacAfter);
+    v[P_NEG] = count(d.fl & kNeg);
+  }
+}
+
+// The workgroup's partials: its waves in order.
+__device__ __forceinline__ void block_partials(const CellDiag& d, gdouble* out, int ntiles,
+                                               int tile) {
   __shared__ double red[kBlock / 64][kNP];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double v[kNP];
+  wave_partials(d, v);
+  if (lane == 0) {
 #pragma unroll
-  for (int s = 0; s < kNP; ++s) {
-    double x = v[s];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const double y = __shfl_xor(x, off, 64);
-      x = is_max_slot(s) ? fmax(x, y) : x + y;
-    }
-    if (lane == 0) red[wave][s] = x;
+    for (int s = 0; s < kNP; ++s) red[wave][s] = v[s];
   }
   __syncthreads();
   if (threadIdx.x < kNP) {
@@ -1201,18 +1131,6 @@ __device__ __forceinline__ void block_partials(double v[kNP], gdouble* out, int 
     for (int w = 1; w < kBlock / 64; ++w) x = is_max_slot(s) ? fmax(x, red[w][s]) : x + red[w][s];
     out[(size_t)s * ntiles + tile] = x;  // slot-major: the reduce reads coalesced
   }
-}
-
-__device__ __forceinline__ void count_solve(double v[kNP], int it, int fl) {
-  if (fl & kNan) v[P_NAN] += 1.0;
-  if (fl & kNeg) v[P_NEG] += 1.0;
-  if (it == 0) return;  // decided before iterating (vacuum or NaN input)
-  v[P_SOLVES] += 1.0;
-  v[P_ITSUM] += (double)it;
-  v[P_ITMAX] = fmax(v[P_ITMAX], (double)it);
-  if (fl & kFallback) v[P_FALLBACK] += 1.0;
-  if (fl & kNonconv) v[P_NONCONV] += 1.0;
-  if (fl & kClamp) v[P_CLAMP] += 1.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1248,20 +1166,12 @@ __global__ __launch_bounds__(kBlock) void k_init_conserved(Fields f, StepParams 
   for (int m = 0; m < 10; ++m) stq_rt(f.pi[m], c, s.e == 0.0 || !visc ? 0.0 : pv[m], f.pf32);
 }
 
-// First step: u*1 from one ideal forward-Euler step; u~^{-1} = 2 u~^0 - u*1.
-template <typename RT, int TX, int TY, int TZ>
-__global__ __launch_bounds__(kBlock) void k_first_estimate(const EventDesc* __restrict__ evs,
-                                                            GroupTable gt) {
-  __shared__ RT lds[lds_doubles<TX, TY, TZ>()];
-  const Ctx cx = load_ctx(evs, gt, 0);
-  const DFields& f = cx.f;
-  const StepParams& p = cx.p;
-  const EosDev& eos = cx.eos;
-  const Geo& g = cx.g;
-  const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile);
+// The thread's cell of the first-step estimate, from its flux divergence R: one ideal
+// forward-Euler step of T~, the root solve, u~^{-1}.
+__device__ __forceinline__ void first_estimate_cell(const DFields& f, const StepParams& p,
+                                                    const EosDev& eos, const Geo& g, const Pos& q,
+                                                    double* R) {
   const double tf = g.cart ? 1.0 : g.tau;
-  double R[14];
-  tile_divergence<RT, TX, TY, TZ, true, false, 0>(f.e, f.u, f.pi, p, eos, tf, q, R, lds);
   const int c = q.c;
   double K[4] = {1.0, 0.0, 0.0, 0.0}, e = 0.0, u1 = 0.0, u2 = 0.0, u3 = 0.0;
   if (q.active) {
@@ -1293,6 +1203,23 @@ __global__ __launch_bounds__(kBlock) void k_first_estimate(const EventDesc* __re
   st_cell(f.up[2] + c, 2.0 * u3 - s.u3);
 }
 
+// First step: u*1 from one ideal forward-Euler step; u~^{-1} = 2 u~^0 - u*1.
+template <typename RT, int TX, int TY, int TZ>
+__global__ __launch_bounds__(kBlock) void k_first_estimate(const EventDesc* __restrict__ evs,
+                                                            GroupTable gt) {
+  __shared__ RT lds[lds_doubles<TX, TY, TZ>()];
+  const Ctx cx = load_ctx(evs, gt, 0);
+  const DFields& f = cx.f;
+  const StepParams& p = cx.p;
+  const EosDev& eos = cx.eos;
+  const Geo& g = cx.g;
+  const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile, threadIdx.x);
+  const double tf = g.cart ? 1.0 : g.tau;
+  double R[14];
+  tile_divergence<RT, TX, TY, TZ, true, false, 0>(f.e, f.u, f.pi, p, eos, tf, q, R, lds);
+  first_estimate_cell(f, p, eos, g, q, R);
+}
+
 // A cell's e, u~ and (VISC) pi~ at the current level; u~ and pi~ read as zero
 // (no loads) where e = 0.
 template <typename RT, bool VISC, int NQ>
@@ -1313,46 +1240,13 @@ __device__ __forceinline__ void cell_values(const DFields& f, int c, double& e, 
   }
 }
 
-// Stage 1 at tau_n (predictor) for the ideal (VISC = false) or viscous path;
-// BK (viscous only): also Pi and n, with P + Pi in T~ and in the root solve.
-// The cell's sources come before the face rounds, so the shear source's
-// gradients and the divergence accumulators are never live together: 137 VGPRs
-// in FP64 (three waves per SIMD, which its 45 KB of LDS also allows; 161 with the
-// sources after the rounds), 103 in FP32 (four waves; 134 before, and the pass
-// went from 0.54 to 0.49 ms on the 201x201x105 hotspot grid), which asks for
-// five (96 VGPRs with 14 spilled: 0.43 -> 0.41 ms there).  The bulk variant
-// and the network variants ask for three waves (uncapped, the matrix-core
-// results take 32 accumulation registers on top; capped, they stay in VGPRs
-// without spills), the network variant with the lambda_1 term two (else one).
-template <typename RT, int TX, int TY, int TZ, bool VISC, bool NET, bool L1, bool BK = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    BK || (NET && !L1) ? 3 : (NET ? 2 : (sizeof(RT) == 4 ? 5 : 1))))) void k_stage1(const EventDesc* __restrict__ evs,
-                                                    GroupTable gt) {
+// Stage 1's sources of the thread's cell into R: the geometric source S_T and the shear
+// relaxation source with its velocity gradients; geo: its S_T^tau (diagnostics).
+template <typename RT, bool VISC, bool L1, bool BK>
+__device__ __forceinline__ void stage1_source(const DFields& f, const StepParams& p,
+                                              const EosDev& eos, const Geo& g, const Pos& q,
+                                              double* R, double& geo) {
   constexpr int NQ = BK ? 12 : 10;
-  __shared__ RT lds[lds_doubles<TX, TY, TZ, 4 + NQ, true>()];
-  const Ctx cx = load_ctx(evs, gt, 0);
-  const DFields& f = cx.f;
-  const StepParams& p = cx.p;
-  const EosDev& eos = cx.eos;
-  const Geo& g = cx.g;
-  const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile);
-  double v[kNP];
-#pragma unroll
-  for (int s = 0; s < kNP; ++s) v[s] = 0.0;
-  const double tf = g.cart ? 1.0 : g.tau;
-  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) {
-    v[P_CFL] = vacuum_cfl<RT>(p, tf) * p.h;  // what the vacuum faces would give
-    // the stage-1 root solve of a quiet cell sees K^tau = T~^{tau tau}/tau_{n+1}
-    if (q.active) v[P_NEG] = f.T[0][q.c] < 0.0 ? 1.0 : 0.0;
-    block_partials(v, f.partial, cx.tg.ntiles, cx.tile);
-    return;
-  }
-  double R[4 + NQ];
-#pragma unroll
-  for (int k = 0; k < 4 + NQ; ++k) R[k] = 0.0;
-  // The cell's sources first (geometric, and the shear relaxation source with its
-  // velocity gradients): their registers are free again before the face rounds
-  // accumulate the flux divergence onto them.
   // e = 0 implies u~ = 0 (the cutoff and the root solve return zero velocity
   // with zero energy density), and pi~ reads as zero there: no loads
   if (q.active) {
@@ -1368,7 +1262,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
       const double see = -(w * u3 * u3 + P + pc[9]);
       R[0] = see;
       R[3] = -(w * ut * u3 + pc[3]);
-      v[P_GEO] = see;
+      geo = see;
     }
     if (VISC && e >= p.eps_cut) {
       double S[NQ];
@@ -1377,12 +1271,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
       for (int m = 0; m < NQ; ++m) R[4 + m] = S[m];
     }
   }
-  const double cfl = tile_divergence<RT, TX, TY, TZ, true, VISC, VISC ? 1 : 0, BK, true, false,
-                                     false>(f.e, f.u, f.pi, p, eos, tf, q, R, lds);
-  v[P_CFL] = cfl * p.h;
-  double K[4] = {1.0, 0.0, 0.0, 0.0}, prev = 0.0, Pi1 = 0.0;
-  double T1[4];
-  bool t1same = true;  // T~' = T~^n bitwise in this cell (no flux or source)
+}
+
+// Stage 1's predictor of the thread's cell from its divergence and sources R: pi~' (stored),
+// T~' (T1) and the root solve's input K = T~'/tau - pi~', start prev and Pi'.
+template <typename RT, bool VISC, bool BK>
+__device__ __forceinline__ void stage1_cell(const DFields& f, const StepParams& p,
+                                            const EosDev& eos, const Geo& g, const Pos& q,
+                                            const double* R, double* K, double* T1, bool& t1same,
+                                            double& prev, double& Pi1) {
+  constexpr int NQ = BK ? 12 : 10;
   if (q.active) {
     const int c = q.c;
     // the cell's values again (cache hits after the face rounds)
@@ -1425,15 +1323,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     for (int nu = 0; nu < 4; ++nu) K[nu] = T1[nu] * inv_tf1 - p1[nu];
     prev = e;
   }
-  // A tile whose T~' equals T~^n in every cell (a vacuum tile: no flux, no
-  // source) does not store it; stage 2T reads T~^n for it instead (the flag is
-  // written every step, so no state carries over between steps).
-  const int all_same = __syncthreads_and(t1same);
-  if (!all_same && q.active) {
-#pragma unroll
-    for (int nu = 0; nu < 4; ++nu) st_cell(f.T1[nu] + q.c, T1[nu]);
-  }
-  if (threadIdx.x == 0) cx.t1same[cx.tile] = all_same;
+}
+
+// Diagnostics of a skipped tile: those its vacuum faces and cells would give (the stage-1
+// root solve of a quiet cell sees K^tau = T~^{tau tau}/tau_{n+1}).
+template <typename RT>
+__device__ __forceinline__ void stage1_asleep(const DFields& f, const StepParams& p, const Pos& q,
+                                              double tf, CellDiag& v) {
+  v.cfl = vacuum_cfl<RT>(p, tf) * p.h;
+  if (q.active) v.fl = f.T[0][q.c] < 0.0 ? kNeg : 0;
+}
+
+// Stage 1's root solve of K (all lanes of a wave call it), e' and u~' stored.
+template <bool NET, bool BK>
+__device__ __forceinline__ void stage1_solve(const DFields& f, const StepParams& p,
+                                             const EosDev& eos, const Pos& q, const double* K,
+                                             double prev, double Pi1, CellDiag& v) {
   const double x0 = root_guess<NET>(p, q.active, K[0], K[1], K[2], K[3], prev);
   if (q.active) {
     const int c = q.c;
@@ -1445,34 +1350,71 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     st_cell(f.u1[1] + c, s.u2);
     st_cell(f.u1[2] + c, s.u3);
   }
-  block_partials(v, f.partial, cx.tg.ntiles, cx.tile);
 }
 
-// Stage 2, part 1 (tau_{n+1}): pi^{n+1} = [ (u^n pi^n + u* pi')/2 + h/2 R_pi(e', u', pi') ] / u'^tau.
-// BK: Pi^{n+1} and n^{n+1} the same way.  The relaxation source comes before the
-// face rounds: 123 VGPRs in FP64 (four waves per SIMD; 139 and three with the
-// source after them: 0.45 -> 0.40 ms on the 201x201x105 hotspot grid, 1.04 ->
-// 0.96 ms without vacuum), 91 in FP32 (five waves: 0.32 -> 0.30 ms).
-template <typename RT, int TX, int TY, int TZ, bool L1, bool BK = false>
-__global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(pi_waves<RT, TX, TY, TZ, BK, BK ? 16 : 14>()))) void k_stage2_pi(
-    const EventDesc* __restrict__ evs, GroupTable gt) {
+// Stage 1 at tau_n (predictor) for the ideal (VISC = false) or viscous path;
+// BK (viscous only): also Pi and n, with P + Pi in T~ and in the root solve.
+// The cell's sources come before the face rounds, so the shear source's
+// gradients and the divergence accumulators are never live together: 137 VGPRs
+// in FP64 (three waves per SIMD, which its 45 KB of LDS also allows; 161 with the
+// sources after the rounds), 103 in FP32 (four waves; 134 before, and the pass
+// went from 0.54 to 0.49 ms on the 201x201x105 hotspot grid), which asks for
+// five (96 VGPRs with 14 spilled: 0.43 -> 0.41 ms there).  The bulk variant
+// and the network variants ask for three waves (uncapped, the matrix-core
+// results take 32 accumulation registers on top; capped, they stay in VGPRs
+// without spills), the network variant with the lambda_1 term two (else one).
+template <typename RT, int TX, int TY, int TZ, bool VISC, bool NET, bool L1, bool BK = false>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
+    BK || (NET && !L1) ? 3 : (NET ? 2 : (sizeof(RT) == 4 ? 5 : 1))))) void k_stage1(const EventDesc* __restrict__ evs,
+                                                    GroupTable gt) {
   constexpr int NQ = BK ? 12 : 10;
-  __shared__ RT lds[lds_doubles<TX, TY, TZ, 4 + NQ>()];
-  const Ctx cx = load_ctx(evs, gt, 1);
+  __shared__ RT lds[lds_doubles<TX, TY, TZ, 4 + NQ, true>()];
+  const Ctx cx = load_ctx(evs, gt, 0);
   const DFields& f = cx.f;
   const StepParams& p = cx.p;
   const EosDev& eos = cx.eos;
   const Geo& g = cx.g;
-  const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile);
-  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) return;
+  const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile, threadIdx.x);
+  CellDiag v;
   const double tf = g.cart ? 1.0 : g.tau;
+  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) {
+    stage1_asleep<RT>(f, p, q, tf, v);
+    block_partials(v, f.partial, cx.tg.ntiles, cx.tile);
+    return;
+  }
   double R[4 + NQ];
 #pragma unroll
   for (int k = 0; k < 4 + NQ; ++k) R[k] = 0.0;
-  // The cell's relaxation source first (as in stage 1: its gradients' registers
-  // are free again before the face rounds accumulate the divergence onto it).
-  // Where e' = 0 the regulator zeroes pi^{n+1} (vac_zero): no source needed.
+  // The cell's sources first: their registers are free again before the face rounds
+  // accumulate the flux divergence onto them.
+  stage1_source<RT, VISC, L1, BK>(f, p, eos, g, q, R, v.geo);
+  const double cfl = tile_divergence<RT, TX, TY, TZ, true, VISC, VISC ? 1 : 0, BK, true, false,
+                                     false>(f.e, f.u, f.pi, p, eos, tf, q, R, lds);
+  v.cfl = cfl * p.h;
+  double K[4] = {1.0, 0.0, 0.0, 0.0}, prev = 0.0, Pi1 = 0.0;
+  double T1[4];
+  bool t1same = true;  // T~' = T~^n bitwise in this cell (no flux or source)
+  stage1_cell<RT, VISC, BK>(f, p, eos, g, q, R, K, T1, t1same, prev, Pi1);
+  // A tile whose T~' equals T~^n in every cell (a vacuum tile: no flux, no
+  // source) does not store it; stage 2T reads T~^n for it instead (the flag is
+  // written every step, so no state carries over between steps).
+  const int all_same = __syncthreads_and(t1same);
+  if (!all_same && q.active) {
+#pragma unroll
+    for (int nu = 0; nu < 4; ++nu) st_cell(f.T1[nu] + q.c, T1[nu]);
+  }
+  if (threadIdx.x == 0) cx.t1same[cx.tile] = all_same;
+  stage1_solve<NET, BK>(f, p, eos, q, K, prev, Pi1, v);
+  block_partials(v, f.partial, cx.tg.ntiles, cx.tile);
+}
+
+// Stage 2pi's relaxation source of the thread's cell into R[4...].  Where e' = 0 the
+// regulator zeroes pi^{n+1} (vac_zero): no source needed.
+template <typename RT, bool L1, bool BK>
+__device__ __forceinline__ void stage2_pi_source(const DFields& f, const StepParams& p,
+                                                 const EosDev& eos, const Geo& g, const Pos& q,
+                                                 double* R) {
+  constexpr int NQ = BK ? 12 : 10;
   if (q.active) {
     const int c = q.c;
     const double e1 = f.e1[c];
@@ -1486,10 +1428,15 @@ __attribute__((amdgpu_waves_per_eu(pi_waves<RT, TX, TY, TZ, BK, BK ? 16 : 14>())
       for (int m = 0; m < NQ; ++m) R[4 + m] = S[m];
     }
   }
-  // pi~' was regulated with e^n in stage 1: zero wherever e^n is (vac_zero)
-  tile_divergence<RT, TX, TY, TZ, false, true, 2, BK, false, false, false>(
-      f.e1, f.u1, f.pi1, p, eos, tf, q, R, lds, f.e);
-  bool quiet = true;  // this cell's part of the quiet-tile test
+}
+
+// Stage 2pi's corrector of the thread's cell: pi~^{n+1}, regulated with e', stored.
+// Returns the cell's part of the quiet-tile test.
+template <typename RT, bool BK>
+__device__ __forceinline__ bool stage2_pi_cell(const DFields& f, const StepParams& p,
+                                               const EosDev& eos, const Pos& q, const double* R) {
+  constexpr int NQ = BK ? 12 : 10;
+  bool quiet = true;
   if (q.active) {
     const int c = q.c;
     const double e1 = f.e1[c];
@@ -1534,50 +1481,52 @@ __attribute__((amdgpu_waves_per_eu(pi_waves<RT, TX, TY, TZ, BK, BK ? 16 : 14>())
 #pragma unroll
     for (int m = 0; m < NQ; ++m) quiet = quiet && pc[m] == 0.0 && pn[m] == 0.0;
   }
+  return quiet;
+}
+
+// Stage 2, part 1 (tau_{n+1}): pi^{n+1} = [ (u^n pi^n + u* pi')/2 + h/2 R_pi(e', u', pi') ] / u'^tau.
+// BK: Pi^{n+1} and n^{n+1} the same way.  The relaxation source comes before the
+// face rounds: 123 VGPRs in FP64 (four waves per SIMD; 139 and three with the
+// source after them: 0.45 -> 0.40 ms on the 201x201x105 hotspot grid, 1.04 ->
+// 0.96 ms without vacuum), 91 in FP32 (five waves: 0.32 -> 0.30 ms).
+template <typename RT, int TX, int TY, int TZ, bool L1, bool BK = false>
+__global__ __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(pi_waves<RT, TX, TY, TZ, BK, BK ? 16 : 14>()))) void k_stage2_pi(
+    const EventDesc* __restrict__ evs, GroupTable gt) {
+  constexpr int NQ = BK ? 12 : 10;
+  __shared__ RT lds[lds_doubles<TX, TY, TZ, 4 + NQ>()];
+  const Ctx cx = load_ctx(evs, gt, 1);
+  const DFields& f = cx.f;
+  const StepParams& p = cx.p;
+  const EosDev& eos = cx.eos;
+  const Geo& g = cx.g;
+  const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile, threadIdx.x);
+  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) return;
+  const double tf = g.cart ? 1.0 : g.tau;
+  double R[4 + NQ];
+#pragma unroll
+  for (int k = 0; k < 4 + NQ; ++k) R[k] = 0.0;
+  // the source first, as in stage 1
+  stage2_pi_source<RT, L1, BK>(f, p, eos, g, q, R);
+  // pi~' was regulated with e^n in stage 1: zero wherever e^n is (vac_zero)
+  tile_divergence<RT, TX, TY, TZ, false, true, 2, BK, false, false, false>(
+      f.e1, f.u1, f.pi1, p, eos, tf, q, R, lds, f.e);
+  const bool quiet = stage2_pi_cell<RT, BK>(f, p, eos, q, R);
   if (p.quiet_r[0] > 0) {
     const int all = __syncthreads_and(quiet);
     if (threadIdx.x == 0) cx.qpi[cx.tile] = all;
   }
 }
 
-// Stage 2, part 2 (tau_{n+1}): T^{n+1} = T^n + [(T' - T^n) + h R_T(e', u', pi^{n+1})]/2,
-// root solve -> (e, u~)^{n+1} (written over e^n and u~^{n-1}), diagnostics.
-// BK: P + Pi^{n+1} in T~ and in the root solve.  The root solve starts from e'
-// in every guess mode (no network instance).
-template <typename RT, int TX, int TY, int TZ, bool VISC, bool BK = false>
-__global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(s2t_waves<RT, TX, TY, TZ, BK>()))) void k_stage2_T(const EventDesc* __restrict__ evs,
-                                                     GroupTable gt) {
-  __shared__ RT lds[lds_doubles_allf<TX, TY, TZ>()];
-  const Ctx cx = load_ctx(evs, gt, 1);
-  const DFields& f = cx.f;
-  const StepParams& p = cx.p;
-  const EosDev& eos = cx.eos;
-  const Geo& g = cx.g;
-  const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile);
-  double v[kNP];
-#pragma unroll
-  for (int s = 0; s < kNP; ++s) v[s] = 0.0;
-  const double tf = g.cart ? 1.0 : g.tau;
-  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) {
-    // the diagnostics the vacuum cells would give; T~ is unchanged
-    v[P_CFL] = vacuum_cfl<RT>(p, tf) * p.h;
-    if (q.active) {
-      v[P_TSUM] = f.T[0][q.c];
-      v[P_VAC] = 1.0;
-      v[P_NEG] = f.T[0][q.c] < 0.0 ? 1.0 : 0.0;  // as the skipped root solve would count
-    }
-    block_partials(v, f.partial + (size_t)kNP * cx.tg.ntiles, cx.tg.ntiles, cx.tile);
-    if (threadIdx.x == 0) cx.qnext[cx.tile] = 1;
-    return;
-  }
+// Stage 2T's corrector of the thread's cell from its divergence R: T~^{n+1} (t1s: T~' was
+// left unstored, equal to T~^n), the root solve, (e, u~)^{n+1} stored.  All lanes of a wave
+// call it.  Returns the cell's part of the quiet-tile test.
+template <typename RT, bool VISC, bool BK>
+__device__ __forceinline__ bool stage2_T_cell(const DFields& f, const StepParams& p,
+                                              const EosDev& eos, const Geo& g, const Pos& q,
+                                              double* R, bool t1s, CellDiag& v) {
   constexpr int NT = BK ? 11 : 10;  // the components T~ uses: pi~ (and Pi)
-  double R[BK ? 16 : 14];
-  const double cfl = tile_divergence<RT, TX, TY, TZ, true, false, VISC ? 2 : 0, BK, false, true>(
-      f.e1, f.u1, f.pi, p, eos, tf, q, R, lds);
-  v[P_CFL] = cfl * p.h;
   double K[4] = {1.0, 0.0, 0.0, 0.0}, prev = 0.0, PiN = 0.0;
-  const bool t1s = cx.t1same[cx.tile] != 0;
   if (q.active) {
     const int c = q.c;
     const double e1 = f.e1[c], u1 = f.u1[0][c], u2 = f.u1[1][c], u3 = f.u1[2][c];
@@ -1599,7 +1548,7 @@ __attribute__((amdgpu_waves_per_eu(s2t_waves<RT, TX, TY, TZ, BK>()))) void k_sta
       const double see = -(w * u3 * u3 + P + pc[9]);
       R[0] += see;
       R[3] += -(w * ut * u3 + pc[3]);
-      v[P_GEO] = see;
+      v.geo = see;
     }
     double Tn[4];
 #pragma unroll
@@ -1619,7 +1568,7 @@ __attribute__((amdgpu_waves_per_eu(s2t_waves<RT, TX, TY, TZ, BK>()))) void k_sta
 #pragma unroll
     for (int nu = 0; nu < 4; ++nu) K[nu] = Tn[nu] * inv_tf1 - pc[nu];
     prev = e1;
-    v[P_TSUM] = Tn[0];
+    v.tsum = Tn[0];
   }
   // the predictor's e' starts the corrector's root solve whatever the guess mode:
   // the two stages' states differ by O(h^2), closer than the learned guess (on the
@@ -1639,14 +1588,279 @@ __attribute__((amdgpu_waves_per_eu(s2t_waves<RT, TX, TY, TZ, BK>()))) void k_sta
     st_cell(f.up[0] + c, s.u1);  // becomes u~^{n+1} after the host swaps u and up
     st_cell(f.up[1] + c, s.u2);
     st_cell(f.up[2] + c, s.u3);
-    v[P_EMAX] = s.e;
-    v[P_VAC] = s.e == 0.0 ? 1.0 : 0.0;
+    v.emax = s.e;
+    if (s.e == 0.0) v.fl |= kVacAfter;
   }
+  return quiet;
+}
+
+// Stage 2T's diagnostics of a skipped tile (T~ is unchanged).
+template <typename RT>
+__device__ __forceinline__ void stage2_T_asleep(const DFields& f, const StepParams& p, const Pos& q,
+                                                double tf, CellDiag& v) {
+  v.cfl = vacuum_cfl<RT>(p, tf) * p.h;
+  if (q.active) {
+    v.tsum = f.T[0][q.c];
+    v.fl = kVacAfter | (v.tsum < 0.0 ? kNeg : 0);  // as the skipped root solve would count
+  }
+}
+
+// Stage 2, part 2 (tau_{n+1}): T^{n+1} = T^n + [(T' - T^n) + h R_T(e', u', pi^{n+1})]/2,
+// root solve -> (e, u~)^{n+1} (written over e^n and u~^{n-1}), diagnostics.
+// BK: P + Pi^{n+1} in T~ and in the root solve.  The root solve starts from e'
+// in every guess mode (no network instance).
+template <typename RT, int TX, int TY, int TZ, bool VISC, bool BK = false>
+__global__ __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(s2t_waves<RT, TX, TY, TZ, BK>()))) void k_stage2_T(const EventDesc* __restrict__ evs,
+                                                     GroupTable gt) {
+  __shared__ RT lds[lds_doubles_allf<TX, TY, TZ>()];
+  const Ctx cx = load_ctx(evs, gt, 1);
+  const DFields& f = cx.f;
+  const StepParams& p = cx.p;
+  const EosDev& eos = cx.eos;
+  const Geo& g = cx.g;
+  const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile, threadIdx.x);
+  CellDiag v;
+  const double tf = g.cart ? 1.0 : g.tau;
+  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) {
+    stage2_T_asleep<RT>(f, p, q, tf, v);
+    block_partials(v, f.partial + (size_t)kNP * cx.tg.ntiles, cx.tg.ntiles, cx.tile);
+    if (threadIdx.x == 0) cx.qnext[cx.tile] = 1;
+    return;
+  }
+  double R[BK ? 16 : 14];
+  const double cfl = tile_divergence<RT, TX, TY, TZ, true, false, VISC ? 2 : 0, BK, false, true>(
+      f.e1, f.u1, f.pi, p, eos, tf, q, R, lds);
+  v.cfl = cfl * p.h;
+  const bool t1s = cx.t1same[cx.tile] != 0;
+  const bool quiet = stage2_T_cell<RT, VISC, BK>(f, p, eos, g, q, R, t1s, v);
   if (p.quiet_r[0] > 0) {
     const int all = __syncthreads_and(quiet);
     if (threadIdx.x == 0) cx.qnext[cx.tile] = all && (!VISC || cx.qpi[cx.tile]);
   }
   block_partials(v, f.partial + (size_t)kNP * cx.tg.ntiles, cx.tg.ntiles, cx.tile);
+}
+
+// ---------------------------------------------------------------------------
+// Small events.  A grid of a few hundred 256-cell tiles leaves most of the chip
+// idle, and each pass then lasts as long as one tile's chain of loads: three or four
+// face rounds one after the other, each a round trip to the caches per pi~ component,
+// then the sources and the root solve.  These kernels shorten the chain instead: a
+// workgroup owns a tile of about 50 cells whose faces fit one round, one wave per axis
+// evaluates that axis' faces, a last wave meanwhile the cells' sources, and after one barrier that wave updates the cells while the
+// face waves have ended and made room for the next workgroup's.  The per-cell arithmetic and its order are those of the large-grid passes (bitwise
+// equal fields).
+// ---------------------------------------------------------------------------
+
+// Faces per axis of a small tile (at most one wave each) and their LDS slots: component
+// k of face f of axis d at k * FT + off_d + f.  TZ = 1: grids of one eta cell only.
+template <int TX, int TY, int TZ>
+struct SmallLayout {
+  static constexpr int F0 = (TX + 1) * TY * TZ, F1 = TX * (TY + 1) * TZ,
+                       F2 = TZ > 1 ? TX * TY * (TZ + 1) : 0;
+  static constexpr int FT = F0 + F1 + F2;
+  static constexpr int AXES = TZ > 1 ? 3 : 2, BLOCK = 64 * (AXES + 1);
+  static_assert(F0 <= 64 && F1 <= 64 && F2 <= 64 && TX * TY * TZ <= 64, "one wave per axis");
+};
+
+template <typename RT, int TX, int TY, int TZ, bool DO_T, bool DO_PI, int PI_SRC, bool BK>
+__device__ __forceinline__ double small_faces(const GField& e, const FSet& u, const FSet& pi,
+                                              const StepParams& p, const EosDev& eos, double tauf,
+                                              const Pos& q, int axis, int f, RT* lds,
+                                              GField ez = GField{nullptr}) {
+  using L = SmallLayout<TX, TY, TZ>;
+  if (axis == 0) {
+    if (p.nx > 1 && f < L::F0)
+      return eval_face<RT, TX, TY, TZ, DO_T, DO_PI, PI_SRC, BK>(e, u, pi, p, eos, tauf, q, 0,
+                                                                      f, lds + f, L::FT, ez);
+  } else if (axis == 1) {
+    if (p.ny > 1 && f < L::F1)
+      return eval_face<RT, TX, TY, TZ, DO_T, DO_PI, PI_SRC, BK>(
+          e, u, pi, p, eos, tauf, q, 1, f, lds + L::F0 + f, L::FT, ez);
+  } else if (TZ > 1) {
+    if (p.ne > 1 && f < L::F2)
+      return eval_face<RT, TX, TY, TZ, DO_T, DO_PI, PI_SRC, BK>(
+          e, u, pi, p, eos, tauf, q, 2, f, lds + L::F0 + L::F1 + f, L::FT, ez);
+  }
+  return 0.0;
+}
+
+template <typename RT, int TX, int TY, int TZ, bool DO_T, bool DO_PI, bool BK>
+__device__ __forceinline__ void small_divergence(const RT* lds, const StepParams& p, double tauf,
+                                                 const Pos& q, double* R) {
+  using L = SmallLayout<TX, TY, TZ>;
+  constexpr int NC = BK ? 16 : 14;
+  if (!q.active) return;
+#pragma unroll
+  for (int d = 0; d < L::AXES; ++d) {
+    const int nd = d == 0 ? p.nx : (d == 1 ? p.ny : p.ne);
+    if (nd == 1) continue;  // both faces see identical states: zero divergence
+    int fm, fp;
+    if (d == 0) {
+      fm = q.lx * (TY * TZ) + q.ly * TZ + q.lz;
+      fp = fm + TY * TZ;
+    } else if (d == 1) {
+      fm = L::F0 + q.lx * ((TY + 1) * TZ) + q.ly * TZ + q.lz;
+      fp = fm + TZ;
+    } else {
+      fm = L::F0 + L::F1 + (q.lx * TY + q.ly) * (TZ + 1) + q.lz;
+      fp = fm + 1;
+    }
+    const RT rinv = (RT)(d == 0 ? p.inv_dx : (d == 1 ? p.inv_dy : p.inv_de / tauf));
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
+      if (k < 4 ? DO_T : DO_PI)
+        R[k] -= (double)((lds[k * L::FT + fp] - lds[k * L::FT + fm]) * rinv);
+  }
+}
+
+// The face waves' end: their largest c h / Delta for the cell wave.  Returns true for them,
+// after the barrier that hands the faces over; false for the cell wave, with the largest
+// of theirs in d.
+template <int AXES>
+__device__ __forceinline__ bool small_handover(int wave, double cfl, double* sh, CellDiag& d) {
+  if (wave < AXES) {
+    cfl = wave_fold(cfl, [](double a, double b) { return fmax(a, b); });
+    if ((threadIdx.x & 63) == 0) sh[wave] = cfl;
+  }
+  __syncthreads();
+  d.cfl = fmax(sh[0], sh[1]);
+  if (AXES == 3) d.cfl = fmax(d.cfl, sh[AXES - 1]);
+  return wave < AXES;
+}
+
+// The cell wave's partials, written without a further barrier.
+__device__ __forceinline__ void small_partials(const CellDiag& d, gdouble* out, int ntiles,
+                                               int tile) {
+  double v[kNP];
+  wave_partials(d, v);
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int s = 0; s < kNP; ++s) out[(size_t)s * ntiles + tile] = v[s];
+  }
+}
+
+// This thread's place in a small workgroup: a wave of faces per axis, then one of cells.
+#define KTMI_SMALL_PROLOGUE(stage2)                                                    \
+  constexpr int AXES = SmallLayout<TX, TY, TZ>::AXES;                                  \
+  const Ctx cx = load_ctx(evs, gt, stage2);                                            \
+  const DFields& f = cx.f;                                                             \
+  const StepParams& p = cx.p;                                                          \
+  const EosDev& eos = cx.eos;                                                          \
+  const Geo& g = cx.g;                                                                 \
+  const int lane = threadIdx.x & 63;                                                   \
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));            \
+  Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile, lane);                               \
+  q.active = q.active && wave == AXES;                                                    \
+  const double tf = g.cart ? 1.0 : g.tau
+
+template <typename RT, int TX, int TY, int TZ>
+__global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_first_estimate_small(
+    const EventDesc* __restrict__ evs, GroupTable gt) {
+  __shared__ RT lds[4 * SmallLayout<TX, TY, TZ>::FT];
+  KTMI_SMALL_PROLOGUE(0);
+  double R[14];
+#pragma unroll
+  for (int k = 0; k < 14; ++k) R[k] = 0.0;
+  if (wave < AXES)
+    small_faces<RT, TX, TY, TZ, true, false, 0, false>(f.e, f.u, f.pi, p, eos, tf, q, wave, lane,
+                                                       lds);
+  __syncthreads();
+  if (wave < AXES) return;
+  small_divergence<RT, TX, TY, TZ, true, false, false>(lds, p, tf, q, R);
+  first_estimate_cell(f, p, eos, g, q, R);
+}
+
+template <typename RT, int TX, int TY, int TZ, bool VISC, bool L1, bool BK = false>
+__global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_stage1_small(const EventDesc* __restrict__ evs,
+                                                              GroupTable gt) {
+  constexpr int NQ = BK ? 12 : 10;
+  __shared__ RT lds[(VISC ? 4 + NQ : 4) * SmallLayout<TX, TY, TZ>::FT];
+  __shared__ double shcfl[3];
+  KTMI_SMALL_PROLOGUE(0);
+  CellDiag v;
+  double R[4 + NQ];
+  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) {
+    if (wave < AXES) return;
+    stage1_asleep<RT>(f, p, q, tf, v);
+    small_partials(v, f.partial, cx.tg.ntiles, cx.tile);
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < 4 + NQ; ++k) R[k] = 0.0;
+  double cfl = 0.0;
+  if (wave < AXES)
+    cfl = small_faces<RT, TX, TY, TZ, true, VISC, VISC ? 1 : 0, BK>(f.e, f.u, f.pi, p, eos, tf, q,
+                                                                    wave, lane, lds) * p.h;
+  else
+    stage1_source<RT, VISC, L1, BK>(f, p, eos, g, q, R, v.geo);
+  if (small_handover<AXES>(wave, cfl, shcfl, v)) return;
+  small_divergence<RT, TX, TY, TZ, true, VISC, BK>(lds, p, tf, q, R);
+  double K[4] = {1.0, 0.0, 0.0, 0.0}, prev = 0.0, Pi1 = 0.0, T1[4];
+  bool t1same = true;
+  stage1_cell<RT, VISC, BK>(f, p, eos, g, q, R, K, T1, t1same, prev, Pi1);
+  if (q.active) {  // T~' always stored (k_stage2_T_small takes it from there)
+#pragma unroll
+    for (int nu = 0; nu < 4; ++nu) st_cell(f.T1[nu] + q.c, T1[nu]);
+  }
+  stage1_solve<false, BK>(f, p, eos, q, K, prev, Pi1, v);
+  small_partials(v, f.partial, cx.tg.ntiles, cx.tile);
+}
+
+template <typename RT, int TX, int TY, int TZ, bool L1, bool BK = false>
+__global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_stage2_pi_small(
+    const EventDesc* __restrict__ evs, GroupTable gt) {
+  constexpr int NQ = BK ? 12 : 10;
+  __shared__ RT lds[(4 + NQ) * SmallLayout<TX, TY, TZ>::FT];
+  KTMI_SMALL_PROLOGUE(1);
+  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) return;
+  double R[4 + NQ];
+#pragma unroll
+  for (int k = 0; k < 4 + NQ; ++k) R[k] = 0.0;
+  if (wave < AXES)
+    small_faces<RT, TX, TY, TZ, false, true, 2, BK>(f.e1, f.u1, f.pi1, p, eos, tf, q, wave, lane,
+                                                    lds, f.e);
+  else
+    stage2_pi_source<RT, L1, BK>(f, p, eos, g, q, R);
+  __syncthreads();
+  if (wave < AXES) return;
+  small_divergence<RT, TX, TY, TZ, false, true, BK>(lds, p, tf, q, R);
+  const bool quiet = stage2_pi_cell<RT, BK>(f, p, eos, q, R);
+  if (p.quiet_r[0] > 0) {
+    const int all = __ballot(!quiet) == 0;
+    if (lane == 0) cx.qpi[cx.tile] = all;
+  }
+}
+
+template <typename RT, int TX, int TY, int TZ, bool VISC, bool BK = false>
+__global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_stage2_T_small(const EventDesc* __restrict__ evs,
+                                                                GroupTable gt) {
+  __shared__ RT lds[4 * SmallLayout<TX, TY, TZ>::FT];
+  __shared__ double shcfl[3];
+  KTMI_SMALL_PROLOGUE(1);
+  CellDiag v;
+  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) {
+    if (wave < AXES) return;
+    stage2_T_asleep<RT>(f, p, q, tf, v);
+    small_partials(v, f.partial + (size_t)kNP * cx.tg.ntiles, cx.tg.ntiles, cx.tile);
+    if (lane == 0) cx.qnext[cx.tile] = 1;
+    return;
+  }
+  double R[BK ? 16 : 14];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) R[k] = 0.0;
+  double cfl = 0.0;
+  if (wave < AXES)
+    cfl = small_faces<RT, TX, TY, TZ, true, false, VISC ? 2 : 0, BK>(f.e1, f.u1, f.pi, p, eos, tf, q,
+                                                                     wave, lane, lds) * p.h;
+  if (small_handover<AXES>(wave, cfl, shcfl, v)) return;
+  small_divergence<RT, TX, TY, TZ, true, false, BK>(lds, p, tf, q, R);
+  const bool quiet = stage2_T_cell<RT, VISC, BK>(f, p, eos, g, q, R, false, v);
+  if (p.quiet_r[0] > 0) {
+    const int all = __ballot(!quiet) == 0;
+    if (lane == 0) cx.qnext[cx.tile] = all && (!VISC || cx.qpi[cx.tile]);
+  }
+  small_partials(v, f.partial + (size_t)kNP * cx.tg.ntiles, cx.tg.ntiles, cx.tile);
 }
 
 // ---------------------------------------------------------------------------
@@ -1661,6 +1875,14 @@ struct TileShape {
 constexpr TileShape kTiles[] = {KTMI_TILE_LIST(KTMI_TILE_ENTRY)};
 #undef KTMI_TILE_ENTRY
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+
+// Tiles of the small-event kernels, launched as tile index kNumTiles + id (internal: the
+// caller's choice is among kTiles).  Their faces fill a wave per axis: 60, 60 and 64 for
+// 4x4x3 (48 cells), 63 and 64 for 8x7 (56 cells; grids of one eta cell).
+#define KTMI_SMALL_TILE_LIST(X) X(0, 4, 4, 3) X(1, 8, 7, 1)
+#define KTMI_TILE_ENTRY(id, X, Y, Z) {X, Y, Z},
+constexpr TileShape kSmallTiles[] = {KTMI_SMALL_TILE_LIST(KTMI_TILE_ENTRY)};
+#undef KTMI_TILE_ENTRY
 
 // Launchers of the stencil passes, one per (pass, arithmetic type), each
 // defined in its own object (ktmi_stencil.hip built per pass and type).  `net`

@@ -44,6 +44,37 @@ void launch_tile(dim3 g, dim3 b, hipStream_t s, const EventDesc* evs, const Grou
 #endif
 }
 
+// The same pass over the small-event tiles: FP64, no network instances.
+template <int X, int Y, int Z, typename RT = KTMI_RT>
+void launch_small(dim3 g, hipStream_t s, const EventDesc* evs, const GroupTable& gt) {
+  const dim3 b(SmallLayout<X, Y, Z>::BLOCK);
+  if constexpr (sizeof(RT) == 8) {
+#if KTMI_PASS == 0
+    hipLaunchKernelGGL((k_first_estimate_small<RT, X, Y, Z>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 1
+    hipLaunchKernelGGL((k_stage1_small<RT, X, Y, Z, true, false>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 2
+    hipLaunchKernelGGL((k_stage1_small<RT, X, Y, Z, false, false>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 3
+    hipLaunchKernelGGL((k_stage2_pi_small<RT, X, Y, Z, false>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 4
+    hipLaunchKernelGGL((k_stage2_T_small<RT, X, Y, Z, true>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 5
+    hipLaunchKernelGGL((k_stage2_T_small<RT, X, Y, Z, false>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 6
+    hipLaunchKernelGGL((k_stage1_small<RT, X, Y, Z, true, true>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 7
+    hipLaunchKernelGGL((k_stage2_pi_small<RT, X, Y, Z, true>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 8
+    hipLaunchKernelGGL((k_stage1_small<RT, X, Y, Z, true, false, true>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 9
+    hipLaunchKernelGGL((k_stage2_pi_small<RT, X, Y, Z, false, true>), g, b, 0, s, evs, gt);
+#elif KTMI_PASS == 10
+    hipLaunchKernelGGL((k_stage2_T_small<RT, X, Y, Z, true, true>), g, b, 0, s, evs, gt);
+#endif
+  }
+}
+
 // only the stage-1 passes without bulk take the network's guess (stage 2T starts
 // its root solve from the predictor's e; the other passes have no root solve)
 constexpr bool kHasNet = KTMI_PASS == 1 || KTMI_PASS == 2 || KTMI_PASS == 6;
@@ -63,6 +94,12 @@ void KTMI_LAUNCH_FN(hipStream_t s, int tile, bool net, const EventDesc* evs,
       launch_tile<X, Y, Z, false>(grid, block, s, evs, gt); \
     break;
     KTMI_TILE_LIST(KTMI_TILE_CASE)
+#undef KTMI_TILE_CASE
+#define KTMI_TILE_CASE(id, X, Y, Z)                \
+  case kNumTiles + id:                             \
+    launch_small<X, Y, Z>(grid, s, evs, gt);       \
+    break;
+    KTMI_SMALL_TILE_LIST(KTMI_TILE_CASE)
 #undef KTMI_TILE_CASE
     default:
       break;

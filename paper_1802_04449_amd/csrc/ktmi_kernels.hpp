@@ -1113,16 +1113,27 @@ __device__ __forceinline__ void wave_partials(const CellDiag& d, double v[kNP]) 
   }
 }
 
+// The geometric source folded ahead of the other partials (stage 1 forms it before the
+// face rounds, where its two registers are dear), for block_partials.
+struct GeoWaves {
+  double w[kBlock / 64];
+};
+__device__ __forceinline__ void fold_geo(double geo, GeoWaves& sh) {
+  double x = 0.0;
+  if (__ballot(geo != 0.0)) x = wave_fold(geo, [](double a, double b) { return a + b; });
+  if ((threadIdx.x & 63) == 0) sh.w[threadIdx.x >> 6] = x;
+}
+
 // The workgroup's partials: its waves in order.
 __device__ __forceinline__ void block_partials(const CellDiag& d, gdouble* out, int ntiles,
-                                               int tile) {
+                                               int tile, const GeoWaves* geo = nullptr) {
   __shared__ double red[kBlock / 64][kNP];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double v[kNP];
   wave_partials(d, v);
   if (lane == 0) {
 #pragma unroll
-    for (int s = 0; s < kNP; ++s) red[wave][s] = v[s];
+    for (int s = 0; s < kNP; ++s) red[wave][s] = geo && s == P_GEO ? geo->w[wave] : v[s];
   }
   __syncthreads();
   if (threadIdx.x < kNP) {
@@ -1369,6 +1380,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
                                                     GroupTable gt) {
   constexpr int NQ = BK ? 12 : 10;
   __shared__ RT lds[lds_doubles<TX, TY, TZ, 4 + NQ, true>()];
+  __shared__ GeoWaves shgeo;
   const Ctx cx = load_ctx(evs, gt, 0);
   const DFields& f = cx.f;
   const StepParams& p = cx.p;
@@ -1387,7 +1399,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
   for (int k = 0; k < 4 + NQ; ++k) R[k] = 0.0;
   // The cell's sources first: their registers are free again before the face rounds
   // accumulate the flux divergence onto them.
-  stage1_source<RT, VISC, L1, BK>(f, p, eos, g, q, R, v.geo);
+  double geo = 0.0;
+  stage1_source<RT, VISC, L1, BK>(f, p, eos, g, q, R, geo);
+  fold_geo(geo, shgeo);
   const double cfl = tile_divergence<RT, TX, TY, TZ, true, VISC, VISC ? 1 : 0, BK, true, false,
                                      false>(f.e, f.u, f.pi, p, eos, tf, q, R, lds);
   v.cfl = cfl * p.h;
@@ -1405,7 +1419,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
   }
   if (threadIdx.x == 0) cx.t1same[cx.tile] = all_same;
   stage1_solve<NET, BK>(f, p, eos, q, K, prev, Pi1, v);
-  block_partials(v, f.partial, cx.tg.ntiles, cx.tile);
+  block_partials(v, f.partial, cx.tg.ntiles, cx.tile, &shgeo);
 }
 
 // Stage 2pi's relaxation source of the thread's cell into R[4...].  Where e' = 0 the

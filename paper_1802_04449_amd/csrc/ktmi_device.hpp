@@ -86,9 +86,9 @@ __device__ __forceinline__ EosSeg eos_seg(const EosDev& q, double e) {
   double x = (e - q.e0) * q.inv_de;
   x = x >= 0.0 ? x : 0.0;  // also maps NaN to the first row
   s.beyond = x >= (double)(q.n - 1);
-  const double xc = s.beyond ? (double)(q.n - 2) : x;  // keeps the index in [0, n-2]
-  int i = (int)floor(xc);
-  i = i > q.n - 2 ? q.n - 2 : (i < 0 ? 0 : i);
+  // 0 <= xc < n - 1, so the truncated index lies in [0, n - 2] without further clamps
+  const double xc = s.beyond ? (double)(q.n - 2) : x;
+  const int i = (int)xc;
   s.i = i;
   s.f = xc - (double)i;
   return s;
@@ -338,8 +338,7 @@ __device__ __forceinline__ void eos_p_cs2_r<float>(const EosDev& q, float e, flo
     cs2 = gl(q.cs2f)[n - 1];
     return;
   }
-  int i = (int)floorf(x);
-  i = i > n - 2 ? n - 2 : (i < 0 ? 0 : i);
+  const int i = (int)x;  // 0 <= x < n - 1: in [0, n - 2]
   const float f = x - (float)i;
   P = gl(q.Pf)[i] + f * (gl(q.Pf)[i + 1] - gl(q.Pf)[i]);
   cs2 = gl(q.cs2f)[i] + f * (gl(q.cs2f)[i + 1] - gl(q.cs2f)[i]);
@@ -371,21 +370,24 @@ __device__ __forceinline__ void eos_p_t_r<float>(const EosDev& q, float e, float
     T = gl(q.Tf)[n - 1] * sqrtf(sqrtf((e + P) / (elast + gl(q.Pf)[n - 1])));
     return;
   }
-  int i = (int)floorf(x);
-  i = i > n - 2 ? n - 2 : (i < 0 ? 0 : i);
+  const int i = (int)x;  // 0 <= x < n - 1: in [0, n - 2]
   const float f = x - (float)i;
   P = gl(q.Pf)[i] + f * (gl(q.Pf)[i + 1] - gl(q.Pf)[i]);
   T = gl(q.Tf)[i] + f * (gl(q.Tf)[i + 1] - gl(q.Tf)[i]);
 }
 
-// min of the three if all are positive, max if all are negative, else 0,
-// written as max(lo, 0) + min(hi, 0) with lo, hi the min and max of the three
-// (no compares or selects; the same value for finite arguments, up to the sign
-// of a zero result).
+// min of the three if all are positive, max if all are negative, else 0: the median of
+// 0 and the min lo and max hi of the three, max(lo, min(hi, 0)) (no compares or selects;
+// the same value for finite arguments, up to the sign of a zero result).
 template <typename R>
 __device__ __forceinline__ R minmod3_r(R a, R b, R c) {
   const R lo = fmin(a, fmin(b, c)), hi = fmax(a, fmax(b, c));
-  return fmax(lo, R(0)) + fmin(hi, R(0));
+  return fmax(lo, fmin(hi, R(0)));
+}
+template <>
+__device__ __forceinline__ float minmod3_r<float>(float a, float b, float c) {
+  const float lo = fminf(a, fminf(b, c)), hi = fmaxf(a, fmaxf(b, c));
+  return __builtin_amdgcn_fmed3f(lo, hi, 0.0f);
 }
 
 template <typename R>

@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kBlock) void k_init_primitive(Fields f, StepParams 
   double P, cs2;
   eos_p_cs2(eos, e, P, cs2);
   if (ext) P += Pi;
-  const double ut = utau(u1, u2, u3);
+  const double ut = utau<false>(u1, u2, u3);
   const double w = e + P;
   const double tf = g.cart ? 1.0 : g.tau;
   const double u4[4] = {ut, u1, u2, u3};

@@ -67,6 +67,53 @@ struct EosDev {
   const float* cs2f;
 };
 
+// ---------------------------------------------------------------------------
+// FP64 reciprocals, quotients and square roots.  FAST (the FP64 passes): from the hardware
+// estimates (v_rcp_f64, v_rsq_f64: about 26 bits), refined with fused multiply-adds to
+// within an ulp.  The arguments here are normal numbers away from the ends of the FP64
+// range, so the scaling and special-case selects of the general sequences (11 and 17
+// instructions) are left out; a zero or infinite divisor gives NaN.  The mixed passes keep
+// the general sequences: their FP32 fluxes amplify a last-bit difference of the FP64 state
+// to FP32 rounding, so that a run would become another sample of it.
+// ---------------------------------------------------------------------------
+template <bool FAST>
+__device__ __forceinline__ double recip(double x) {
+  if constexpr (!FAST) return 1.0 / x;
+  const double y = __builtin_amdgcn_rcp(x);
+  const double e = __builtin_fma(-x, y, 1.0);
+  return __builtin_fma(y, __builtin_fma(e, e, e), y);  // y (1 + e + e^2)
+}
+template <bool FAST>
+__device__ __forceinline__ double quot(double a, double b) {
+  if constexpr (!FAST) return a / b;
+  const double y = recip<true>(b), q = a * y;
+  return __builtin_fma(__builtin_fma(-b, q, a), y, q);  // residual correction
+}
+// sqrt(x), x > 0: one Goldschmidt step on (x y, y / 2), then a residual correction.
+template <bool FAST>
+__device__ __forceinline__ double root(double x) {
+  if constexpr (!FAST) return sqrt(x);
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+}
+// 1 / sqrt(x), x > 0: y (1 + e/2 + 3 e^2/8), e = 1 - x y^2.
+template <bool FAST>
+__device__ __forceinline__ double inv_root(double x) {
+  if constexpr (!FAST) return 1.0 / sqrt(x);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = __builtin_fma(-(x * y), y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
+// Whether the passes of precision RT take them, and sqrt in the passes' flux type.
+template <typename RT>
+constexpr bool kFast = sizeof(RT) == 8;
+__device__ __forceinline__ double root_r(double x) { return root<true>(x); }
+__device__ __forceinline__ float root_r(float x) { return sqrt(x); }
+
 // Root-solve outcome flags (counted in the diagnostics).  kNeg: K^tau < 0.
 enum : int { kFallback = 1, kNonconv = 2, kNan = 4, kVac = 8, kClamp = 16, kNeg = 32 };
 
@@ -184,7 +231,7 @@ struct Prim {
 
 __device__ __forceinline__ Prim vacuum() { return Prim{0.0, 0.0, 0.0, 0.0}; }
 
-template <bool BK = false>
+template <bool FAST, bool BK = false>
 __device__ inline Prim con2prim(const EosDev& q, const StepParams& p, double E, double K1,
                                 double K2, double K3, double guess, int& iters, int& flags,
                                 double Pi = 0.0) {
@@ -216,7 +263,7 @@ __device__ inline Prim con2prim(const EosDev& q, const StepParams& p, double E, 
     M2 = K1 * K1 + K2 * K2 + K3 * K3;
     flags |= kClamp;
   }
-  double lo = E - M2 / B;
+  double lo = E - quot<FAST>(M2, B);
   lo = lo < 0.0 ? 0.0 : lo;
   double hi = E;
   const double lo0 = lo, hi0 = hi;
@@ -233,7 +280,7 @@ __device__ inline Prim con2prim(const EosDev& q, const StepParams& p, double E, 
     }
     double P, dP;
     eos_p_dp(q, x, P, dP);
-    const double r = 1.0 / (BK ? (E + P) + Pi : E + P);  // one division for f and f'
+    const double r = recip<FAST>(BK ? (E + P) + Pi : E + P);  // one division for f and f'
     const double f = x - E + M2 * r;
     const double df = 1.0 - M2 * dP * r * r;
     if (f == 0.0) {
@@ -244,7 +291,7 @@ __device__ inline Prim con2prim(const EosDev& q, const StepParams& p, double E, 
       hi = x;
     else
       lo = x;
-    double xn = x - f / df;
+    double xn = x - quot<FAST>(f, df);
     if (!(xn >= lo && xn <= hi)) {
       xn = 0.5 * (lo + hi);
       flags |= kFallback;
@@ -263,10 +310,10 @@ __device__ inline Prim con2prim(const EosDev& q, const StepParams& p, double E, 
   {
     double P, dP;
     eos_p_dp(q, x, P, dP);
-    const double r = 1.0 / (BK ? (E + P) + Pi : E + P);
+    const double r = recip<FAST>(BK ? (E + P) + Pi : E + P);
     const double f = x - E + M2 * r;
     const double df = 1.0 - M2 * dP * r * r;
-    const double xp = x - f / df;
+    const double xp = x - quot<FAST>(f, df);
     if (xp >= lo0 && xp <= hi0) x = xp;
   }
   iters = it + 1;
@@ -275,7 +322,7 @@ __device__ inline Prim con2prim(const EosDev& q, const StepParams& p, double E, 
     return vacuum();
   }
   const double P = BK ? eos_p(q, x) + Pi : eos_p(q, x);
-  const double inv = 1.0 / sqrt((E + P) * (x + P));
+  const double inv = inv_root<FAST>((E + P) * (x + P));
   return Prim{x, K1 * inv, K2 * inv, K3 * inv};
 }
 
@@ -344,6 +391,55 @@ __device__ __forceinline__ void eos_p_cs2_r<float>(const EosDev& q, float e, flo
   cs2 = gl(q.cs2f)[i] + f * (gl(q.cs2f)[i + 1] - gl(q.cs2f)[i]);
 }
 
+// P and cs2 of the two states of a face: their table rows loaded together unless a lane of
+// the wave lies past the table's end.
+template <typename R>
+__device__ __forceinline__ void eos_p_cs2_pair(const EosDev& q, R e0, R e1, R* P, R* c) {
+  if (q.kind == 1) {
+    const R last = (R)(q.n - 1);
+    R x[2], f[2];
+    int i[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      R e = s ? e1 : e0;
+      e = e > R(0) ? e : R(0);
+      if constexpr (sizeof(R) == 8)
+        x[s] = (e - q.e0) * q.inv_de;
+      else
+        x[s] = (e - q.e0_f) * q.inv_de_f;
+      x[s] = x[s] >= R(0) ? x[s] : R(0);
+    }
+    if (__ballot(x[0] >= last || x[1] >= last) == 0) {
+      const R *tp, *tc;
+      if constexpr (sizeof(R) == 8) {
+        tp = q.P;
+        tc = q.cs2;
+      } else {
+        tp = q.Pf;
+        tc = q.cs2f;
+      }
+      R p0[2], p1[2], c0[2], c1[2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        i[s] = (int)x[s];  // 0 <= x < n - 1: in [0, n - 2]
+        f[s] = x[s] - (R)i[s];
+        p0[s] = gl(tp)[i[s]];
+        p1[s] = gl(tp)[i[s] + 1];
+        c0[s] = gl(tc)[i[s]];
+        c1[s] = gl(tc)[i[s] + 1];
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        P[s] = p0[s] + f[s] * (p1[s] - p0[s]);
+        c[s] = c0[s] + f[s] * (c1[s] - c0[s]);
+      }
+      return;
+    }
+  }
+  eos_p_cs2_r<R>(q, e0, P[0], c[0]);
+  eos_p_cs2_r<R>(q, e1, P[1], c[1]);
+}
+
 template <typename R>
 __device__ __forceinline__ void eos_p_t_r(const EosDev& q, R e, R& P, R& T);
 
@@ -401,6 +497,8 @@ __device__ __forceinline__ R local_speed_r(R ut, R ux, R uy, R ue, R ud, R cs2) 
   const R u2 = ux * ux + uy * uy + ue * ue;
   const R up2 = u2 - ud * ud;  // transverse part (>= 0 up to rounding)
   const R disc = R(1) + (up2 > R(0) ? up2 : R(0)) * w;
+  if constexpr (sizeof(R) == 8)  // (cs2 may be zero)
+    return quot<true>(fabs(ud) * w * ut + root<true>(cs2 * disc + 1e-280), R(1) + u2 * w);
   return (fabs(ud) * w * ut + sqrt(cs2 * disc)) / (R(1) + u2 * w);
 }
 

@@ -342,6 +342,53 @@ __device__ __forceinline__ double ld_pi(const FSet& pi, int m, int idx, double e
   return v;
 }
 
+// The pi~ components in T~'s density (tau nu) and flux (axis nu), by axis, increasing.
+__device__ constexpr int kFluxComp[3][7] = {
+    {0, 1, 2, 3, 4, 5, 6}, {0, 1, 2, 3, 5, 7, 8}, {0, 1, 2, 3, 6, 8, 9}};
+
+// How a face evaluation loads, by pass (measured on 201x201x105 hotspots / 101x99x65
+// without vacuum, us a pass, with all of the others):
+//   OFF32: offsets kept as 32 bits up to each load (below); FP64 stage 1 424.9 -> 422.2 /
+//     179.0 -> 176.4, stage 2T 331 -> 327 / 115.5 -> 112.8, FP32 stage 1 346 -> 327; not the
+//     FP32 stage 2pi (284 -> 300).
+//   UMASK: a wave with no vacuum in its stencils branches around pi~'s masks; FP64 stage 1
+//     -> 174.6 without vacuum, FP32 stage 1 327 -> 319; not the FP32 stage 2pi (284 -> 312).
+//   EOSF: the EoS rows of both states looked up together, ahead of u~'s arithmetic, so
+//     that their round trip is u~'s; FP64 stage 1 421 -> 418 / 174.6 -> 172.5, stage 2pi
+//     386 -> 380 / 158 -> 153.7; not stage 2T (it spills: 328 -> 398) nor FP32 (319 -> 324).
+//   PF: pi~ components in flight; two in FP64: stage 1 418 -> 411 / 172.5 -> 168.3, stage 2pi
+//     380 -> 376 / 153.7 -> 149.2; FP32 has no registers for it.
+template <typename R, bool DO_T, bool DO_PI>
+struct FaceLoads {
+  static constexpr bool F64 = sizeof(R) == 8;
+  static constexpr bool OFF32 = F64 || DO_T;
+  static constexpr bool UMASK = DO_PI && (F64 || DO_T);
+  static constexpr bool EOSF = DO_PI && F64;
+  static constexpr int PF = DO_PI && F64 ? 2 : 1;
+};
+
+// The four cells of a face stencil, loaded from any field.
+template <bool OFF32>
+struct StencilIdx {
+  unsigned off[4];  // byte offsets of an FP64 field's elements
+  __device__ __forceinline__ void set(int t, int i) { off[t] = (unsigned)i * 8u; }
+  // the offset made anew: a 64-bit copy of it, kept from an earlier block, would cost
+  // each load an address addition per lane instead of the scalar-base form
+  __device__ __forceinline__ void touch(int t) {
+    if constexpr (OFF32) asm volatile("" : "+v"(off[t]));
+  }
+  __device__ __forceinline__ double ld(const GField& g, int t) {
+    touch(t);
+    return *(const gdouble*)((const gchar*)g.p + off[t]);
+  }
+  template <typename RT>
+  __device__ __forceinline__ double ldq(const GField& g, int t) {
+    touch(t);
+    if constexpr (sizeof(RT) == 4) return (double)*(const gfloat*)((const gchar*)g.p + (off[t] >> 1));
+    return *(const gdouble*)((const gchar*)g.p + off[t]);
+  }
+};
+
 // KT face flux H = [F(Q^r) + F(Q^l)]/2 - c (Q^r - Q^l)/2 (Sec. III, eq. flux_out)
 // at the face between cells a and a+1 along `axis` (1 = x, 2 = y, 3 = eta),
 // from a minmod reconstruction of the primitives on the 4-cell stencil
@@ -354,20 +401,21 @@ __device__ __forceinline__ double ld_pi(const FSet& pi, int m, int idx, double e
 // (k = 15); both have the flux form of the pi~ components.
 //
 // Evaluated as a stream to keep few values live: e and u~ first (face states,
-// u~^tau, P, c_s^2, e + P, speeds, the fluid part of T~'s Q and F), then one
-// pi~ component at a time (its face states, its own flux, its terms in T~'s Q
-// and F), then T~'s flux.  The arithmetic of every component is that of
-// tau (w u u - P g + pi) and u pi as written, in that order.
+// u~^tau, P, c_s^2, e + P, speeds, the fluid part of T~'s flux), then one
+// pi~ component at a time (its face states, its own flux, its terms in T~'s
+// flux), then T~'s flux.
 template <typename R, bool DO_T, bool DO_PI, int PI_SRC, bool BK = false>
 __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
                                        const FSet& pi, int base, int a, int n,
                                        int stride, int axis, R tauf, const StepParams& p,
                                        const EosDev& eos, R* out, int F,
                                        GField ez = GField{nullptr}) {
-  int idx[4];
+  using FL = FaceLoads<R, DO_T, DO_PI>;
+  StencilIdx<FL::OFF32> ix;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) idx[t] = base + clampi(a - 1 + t, 0, n - 1) * stride;
+  for (int t = 0; t < 4; ++t) ix.set(t, base + clampi(a - 1 + t, 0, n - 1) * stride);
   constexpr int NQ = BK ? 12 : 10;
+  constexpr bool F64 = sizeof(R) == 8;
   // Vacuum faces: every state the kernels write has u~ = 0 where e = 0, and
   // pi~ reads as zero there (PI_SRC 0/1; as stored in stage 2T, whose pi^{n+1}
   // the regulator zeroed wherever e' is zero), so e alone decides and a vacuum
@@ -376,7 +424,7 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
   bool vac = true;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    ev[t] = e[idx[t]];
+    ev[t] = ix.ld(e, t);
     vac = vac && (ev[t] == 0.0);
   }
   // As-stored pi~ (PI_SRC 2) is zero wherever the energy density it was
@@ -390,11 +438,11 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
   double ezv[4] = {1.0, 1.0, 1.0, 1.0};
   if (zmask) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) ezv[t] = ez[idx[t]];
+    for (int t = 0; t < 4; ++t) ezv[t] = ix.ld(ez, t);
   }
   if (PI_SRC == 2 && vac && ez.p != nullptr && p.vac_zero) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) vac = vac && (zmask ? ezv[t] : ez[idx[t]]) == 0.0;
+    for (int t = 0; t < 4; ++t) vac = vac && (zmask ? ezv[t] : ix.ld(ez, t)) == 0.0;
   }
   if (vac && (PI_SRC != 2 || p.vac_zero)) {
 #pragma unroll
@@ -403,77 +451,118 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
     return (R)p.c_vac;
   }
   const R th = (R)p.theta;
-  // the pi~ components the face needs; the first one's loads go out with u~'s
+  // the pi~ components (and n) the face needs, in increasing order: all of them, or those
+  // of T~'s density (tau nu) and flux (axis nu); Pi comes with e and u~ below
+  constexpr int NN = PI_SRC == 0 ? 0 : (DO_PI ? (BK ? 11 : 10) : 7);
+  auto comp = [&](int k) { return DO_PI ? (k < 10 ? k : 11) : kFluxComp[axis - 1][k]; };
+  // WALK (FP32 stage 2T): the components found by walking over all of them, which leaves
+  // T~'s sums in blocks of their own: the compiler's contractions there, and so the mixed
+  // path's rounding, depend on it.  4 us of 280 a pass against the list.
+  constexpr bool WALK = !F64 && DO_T && !DO_PI;
   auto needed = [&](int m) {
-    if (m == 10 || PI_SRC == 0) return false;  // Pi: with e and u~ below
+    if (m == 10 || PI_SRC == 0) return false;
     bool inT = false;
 #pragma unroll
     for (int nu = 0; nu < 4; ++nu) inT = inT || m == sym(0, nu) || m == sym(axis, nu);
-    return DO_PI || (DO_T && inT);
+    return inT;
   };
   auto next_needed = [&](int m) {
     int k = m + 1;
     while (k < NQ && !needed(k)) ++k;
     return k;
   };
-  double pcur[4], pnext[4];
-  // e and u~ face states (and Pi's, which T~'s pressure needs)
+  double pcur[4], pnext[4];  // WALK's components in flight
+  constexpr int PF = FL::PF;
+  double pb[PF + 1][4];  // pi~ components in flight, by their order modulo PF + 1
+  auto fetch = [&](int k) {  // the k-th needed component
+    if (k < NN) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) pb[k % (PF + 1)][t] = ix.template ldq<R>(pi[comp(k)], t);
+    }
+  };
+  // u~'s loads and the first pi~ components' go out before the EoS lookups, which need
+  // only e
   constexpr int NV = BK ? 5 : 4;
-  R fL[NV], fR[NV];
-  {
-    R q4[NV][4];
+  double uq[3][4], Pq[BK ? 4 : 1];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) q4[0][t] = (R)ev[t];
+  for (int m = 0; m < 3; ++m)
 #pragma unroll
-    for (int m = 0; m < 3; ++m)
+    for (int t = 0; t < 4; ++t) uq[m][t] = ix.ld(u[m], t);
+  if constexpr (WALK) {
+    const int m0 = next_needed(-1);
+    if (m0 < NQ) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) q4[1 + m][t] = (R)u[m][idx[t]];
-    {
-      const int m0 = next_needed(-1);
-      if (m0 < NQ) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) pcur[t] = ldq<R>(pi[m0], idx[t]);
-      }
+      for (int t = 0; t < 4; ++t) pcur[t] = ix.template ldq<R>(pi[m0], t);
     }
-    if constexpr (BK) {
+  } else {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) q4[4][t] = (R)ld_pi<PI_SRC, R>(pi, 10, idx[t], ev[t]);
-    }
+    for (int k = 0; k < PF; ++k) fetch(k);
+  }
+  if constexpr (BK) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      fL[v] = q4[v][1] + R(0.5) * mm_slope_r<R>(th, q4[v][0], q4[v][1], q4[v][2]);
-      fR[v] = q4[v][2] - R(0.5) * mm_slope_r<R>(th, q4[v][1], q4[v][2], q4[v][3]);
+    for (int t = 0; t < 4; ++t) {
+      Pq[t] = ix.template ldq<R>(pi[10], t);
+      if (PI_SRC == 1 && ev[t] == 0.0) Pq[t] = 0.0;
     }
   }
-  R ut[2], ud[2], AQ[2][4], AF[2][4], sp[2];
+  R fL[NV], fR[NV], Ps[2], cs2s[2];
+  fL[0] = (R)ev[1] + R(0.5) * mm_slope_r<R>(th, (R)ev[0], (R)ev[1], (R)ev[2]);
+  fR[0] = (R)ev[2] - R(0.5) * mm_slope_r<R>(th, (R)ev[1], (R)ev[2], (R)ev[3]);
+  if constexpr (FL::EOSF) eos_p_cs2_pair<R>(eos, fL[0], fR[0], Ps, cs2s);
+#pragma unroll
+  for (int v = 1; v < NV; ++v) {
+    R q4[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) q4[t] = (R)(v < 4 ? uq[v < 4 ? v - 1 : 0][t] : Pq[BK ? t : 0]);
+    fL[v] = q4[1] + R(0.5) * mm_slope_r<R>(th, q4[0], q4[1], q4[2]);
+    fR[v] = q4[2] - R(0.5) * mm_slope_r<R>(th, q4[1], q4[2], q4[3]);
+  }
+  if constexpr (!FL::EOSF) {
+    eos_p_cs2_r<R>(eos, fL[0], Ps[0], cs2s[0]);
+    eos_p_cs2_r<R>(eos, fR[0], Ps[1], cs2s[1]);
+  }
+  R ut[2], ud[2], AQ[F64 ? 1 : 2][4], AF[F64 ? 1 : 2][4], sp[2], w[2], P[2];
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
     const R* q = side ? fR : fL;
     const R ux = q[1], uy = q[2], ue = q[3];
-    ut[side] = sqrt(R(1) + ux * ux + uy * uy + ue * ue);
-    R P, cs2;
-    eos_p_cs2_r<R>(eos, q[0], P, cs2);
-    if constexpr (BK) P = P + q[4];  // P + Pi
-    const R w = (q[0] > R(0) ? q[0] : R(0)) + P;
+    ut[side] = root_r(R(1) + ux * ux + uy * uy + ue * ue);
+    P[side] = Ps[side];
+    const R cs2 = cs2s[side];
+    if constexpr (BK) P[side] = P[side] + q[4];  // P + Pi
+    w[side] = (q[0] > R(0) ? q[0] : R(0)) + P[side];
     const R u4[4] = {ut[side], ux, uy, ue};
     ud[side] = u4[axis];
-    if (DO_T) {
+    if constexpr (DO_T && !F64) {
 #pragma unroll
       for (int nu = 0; nu < 4; ++nu) {
-        AQ[side][nu] = w * ut[side] * u4[nu] - (nu == 0 ? P : R(0));
-        AF[side][nu] = w * ud[side] * u4[nu] + (nu == axis ? P : R(0));
+        AQ[side][nu] = w[side] * ut[side] * u4[nu] - (nu == 0 ? P[side] : R(0));
+        AF[side][nu] = w[side] * ud[side] * u4[nu] + (nu == axis ? P[side] : R(0));
       }
     }
     sp[side] = local_speed_r<R>(ut[side], ux, uy, ue, ud[side], cs2);
   }
   const R c = fmax(sp[0], sp[1]);
-  // flux of a transported field with face states pL, pR: Q = u~^tau p, F = u~^axis p.  In
+  // Flux of a transported field with face states pL, pR: Q = u~^tau p, F = u~^axis p.  In
   // FP64 with the two states' coefficients formed once per face (2 operations per field
-  // instead of 8); FP32 keeps the written order, whose rounding is what the mixed path's
-  // results are made of.
-  const R kL = R(0.5) * (ud[0] + c * ut[0]), kR = R(0.5) * (ud[1] - c * ut[1]);
+  // instead of 8), and T~'s flux as one sum over both states, 2 H / tau =
+  // sum_s [w u^nu (u^axis + s c u^tau) + P (g^{axis nu} - s c g^{0 nu}) + pi^{axis nu} + s c pi^{0 nu}]
+  // with s = +1 left, -1 right: 4 accumulators instead of both states' Q and F.  FP32 keeps
+  // the written order, whose rounding is what the mixed path's results are made of.
+  const R k2L = ud[0] + c * ut[0], k2R = ud[1] - c * ut[1];
+  const R kL = R(0.5) * k2L, kR = R(0.5) * k2R;
+  R H[4];
+  if constexpr (DO_T && F64) {
+    const R aL = w[0] * k2L, aR = w[1] * k2R;
+    H[0] = (aL * ut[0] + aR * ut[1]) + c * (P[1] - P[0]);
+#pragma unroll
+    for (int nu = 1; nu < 4; ++nu) {
+      H[nu] = aL * fL[nu] + aR * fR[nu];
+      if (nu == axis) H[nu] = H[nu] + (P[0] + P[1]);
+    }
+  }
   auto flux = [&](R pL, R pR) {
-    if constexpr (sizeof(R) == 8) {
+    if constexpr (F64) {
       return kL * pL + kR * pR;
     } else {
       const R QL = ut[0] * pL, QR = ut[1] * pR;
@@ -484,28 +573,36 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
   if constexpr (BK) {
     if (DO_PI) out[14 * F] = flux(fL[4], fR[4]);  // Pi's own flux
   }
-  // pi~ components (and n), one at a time; the next needed component's loads
-  // are issued before the current one is used, so one round trip to the cache
-  // overlaps the arithmetic of the previous component
-#pragma unroll
-  for (int m = 0; m < NQ; ++m) {
-    if (!needed(m)) {  // no pi~ (ideal), Pi, or a component T~'s flux does not use
-      if (DO_PI && m != 10) out[(4 + m) * F] = R(0);
-      continue;
-    }
-    const int mn = next_needed(m);
-    if (mn < NQ) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) pnext[t] = ldq<R>(pi[mn], idx[t]);
-    }
-    R p4[4];
+  // pi~ components (and n), one at a time; the loads of the component PF places on are
+  // issued before the current one is used, so round trips to the caches overlap the
+  // arithmetic
+  bool mask = true;
+  if constexpr (FL::UMASK) {
+    bool mk = false;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
-      p4[t] = (R)((PI_SRC == 1 && ev[t] == 0.0) || (zmask && ezv[t] == 0.0) ? 0.0 : pcur[t]);
-    const R pL = p4[1] + R(0.5) * mm_slope_r<R>(th, p4[0], p4[1], p4[2]);
-    const R pR = p4[2] - R(0.5) * mm_slope_r<R>(th, p4[1], p4[2], p4[3]);
-    if (DO_PI) out[(4 + m) * F] = flux(pL, pR);
-    if (DO_T) {
+      mk = mk || (PI_SRC == 1 && ev[t] == 0.0) || (zmask && ezv[t] == 0.0);
+    mask = __ballot(mk) != 0;
+  }
+  if constexpr (DO_PI && NN == 0) {  // no pi~ (ideal)
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) out[(4 + m) * F] = R(0);
+  }
+  if constexpr (WALK) {
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) {
+      if (!needed(m)) continue;
+      const int mn = next_needed(m);
+      if (mn < NQ) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) pnext[t] = ix.template ldq<R>(pi[mn], t);
+      }
+      R p4[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        p4[t] = (R)((PI_SRC == 1 && ev[t] == 0.0) || (zmask && ezv[t] == 0.0) ? 0.0 : pcur[t]);
+      const R pL = p4[1] + R(0.5) * mm_slope_r<R>(th, p4[0], p4[1], p4[2]);
+      const R pR = p4[2] - R(0.5) * mm_slope_r<R>(th, p4[1], p4[2], p4[3]);
 #pragma unroll
       for (int nu = 0; nu < 4; ++nu) {
         if (m == sym(0, nu)) {
@@ -517,15 +614,52 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
           AF[1][nu] = AF[1][nu] + pR;
         }
       }
-    }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) pcur[t] = pnext[t];
+      for (int t = 0; t < 4; ++t) pcur[t] = pnext[t];
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < NN; ++k) {
+      const int m = comp(k);
+      fetch(k + PF);
+      double* const pc = pb[k % (PF + 1)];
+      if (mask) {
+        if constexpr (FL::UMASK) asm volatile("");  // keeps the branch a branch
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if ((PI_SRC == 1 && ev[t] == 0.0) || (zmask && ezv[t] == 0.0)) pc[t] = 0.0;
+      }
+      R p4[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) p4[t] = (R)pc[t];
+      const R pL = p4[1] + R(0.5) * mm_slope_r<R>(th, p4[0], p4[1], p4[2]);
+      const R pR = p4[2] - R(0.5) * mm_slope_r<R>(th, p4[1], p4[2], p4[3]);
+      if (DO_PI) out[(4 + m) * F] = flux(pL, pR);
+      if constexpr (DO_T) {
+#pragma unroll
+        for (int nu = 0; nu < 4; ++nu) {
+          if constexpr (F64) {
+            if (m == sym(0, nu)) H[nu] = H[nu] + c * (pL - pR);
+            if (m == sym(axis, nu)) H[nu] = H[nu] + (pL + pR);
+          } else {
+            if (m == sym(0, nu)) {
+              AQ[0][nu] = AQ[0][nu] + pL;
+              AQ[1][nu] = AQ[1][nu] + pR;
+            }
+            if (m == sym(axis, nu)) {
+              AF[0][nu] = AF[0][nu] + pL;
+              AF[1][nu] = AF[1][nu] + pR;
+            }
+          }
+        }
+      }
+    }
   }
 #pragma unroll
   for (int nu = 0; nu < 4; ++nu) {
-    if constexpr (DO_T && sizeof(R) == 8) {
-      out[nu * F] = (R(0.5) * tauf) * ((AF[0][nu] + AF[1][nu]) - c * (AQ[1][nu] - AQ[0][nu]));
-    } else if (DO_T) {
+    if constexpr (DO_T && F64) {
+      out[nu * F] = (R(0.5) * tauf) * H[nu];
+    } else if constexpr (DO_T) {
       const R Q0 = tauf * AQ[0][nu], Q1 = tauf * AQ[1][nu];
       const R F0 = tauf * AF[0][nu], F1 = tauf * AF[1][nu];
       out[nu * F] = R(0.5) * (F0 + F1) - R(0.5) * c * (Q1 - Q0);
@@ -877,9 +1011,15 @@ constexpr int s2t_waves() {
   return !BK ? (sizeof(RT) == 4 ? 5 : 4) : pi_waves<RT, TX, TY, TZ, false>();
 }
 
-// u~^tau of spatial components.
+// u~^tau of spatial components, and its reciprocal.
+template <bool FAST>
 __device__ __forceinline__ double utau(double a, double b, double c) {
-  return sqrt(1.0 + a * a + b * b + c * c);
+  return root<FAST>(1.0 + a * a + b * b + c * c);
+}
+template <bool FAST>
+__device__ __forceinline__ double inv_utau(double a, double b, double c) {
+  if constexpr (!FAST) return 1.0 / utau<false>(a, b, c);
+  return inv_root<FAST>(1.0 + a * a + b * b + c * c);
 }
 
 // Israel-Stewart source (Sec. II, eqns. pitilde, Ipi; eqn. pimn with lambda_2 = lambda_3 = 0):
@@ -909,13 +1049,13 @@ __device__ __forceinline__ void pi_source(const FSet& u, const FSet& uE,
   const int cart = g.cart;
   const R inv_tau = (R)(1.0 / g.tau);
   const R u1c = (R)u[0][c0], u2c = (R)u[1][c0], u3c = (R)u[2][c0];
-  const R uc[4] = {sqrt(R(1) + u1c * u1c + u2c * u2c + u3c * u3c), u1c, u2c, u3c};
+  const R uc[4] = {root_r(R(1) + u1c * u1c + u2c * u2c + u3c * u3c), u1c, u2c, u3c};
   R G[4][4];
   {
     const R a1 = (R)uE[0][c0], a2 = (R)uE[1][c0], a3 = (R)uE[2][c0];
     const R b1 = (R)uL[0][c0], b2 = (R)uL[1][c0], b3 = (R)uL[2][c0];
-    const R ea[4] = {sqrt(R(1) + a1 * a1 + a2 * a2 + a3 * a3), a1, a2, a3};
-    const R eb[4] = {sqrt(R(1) + b1 * b1 + b2 * b2 + b3 * b3), b1, b2, b3};
+    const R ea[4] = {root_r(R(1) + a1 * a1 + a2 * a2 + a3 * a3), a1, a2, a3};
+    const R eb[4] = {root_r(R(1) + b1 * b1 + b2 * b2 + b3 * b3), b1, b2, b3};
     const R ih = (R)p.inv_h;
 #pragma unroll
     for (int nu = 0; nu < 4; ++nu) G[0][nu] = (eb[nu] - ea[nu]) * ih;
@@ -931,8 +1071,8 @@ __device__ __forceinline__ void pi_source(const FSet& u, const FSet& uE,
     const int im = c0 + (clampi(co[d] - 1, 0, n3[d] - 1) - co[d]) * st[d];
     const R p1 = (R)u[0][ip], p2 = (R)u[1][ip], p3 = (R)u[2][ip];
     const R m1 = (R)u[0][im], m2 = (R)u[1][im], m3 = (R)u[2][im];
-    const R up4[4] = {sqrt(R(1) + p1 * p1 + p2 * p2 + p3 * p3), p1, p2, p3};
-    const R um4[4] = {sqrt(R(1) + m1 * m1 + m2 * m2 + m3 * m3), m1, m2, m3};
+    const R up4[4] = {root_r(R(1) + p1 * p1 + p2 * p2 + p3 * p3), p1, p2, p3};
+    const R um4[4] = {root_r(R(1) + m1 * m1 + m2 * m2 + m3 * m3), m1, m2, m3};
 #pragma unroll
     for (int nu = 0; nu < 4; ++nu) G[d + 1][nu] = (up4[nu] - um4[nu]) * ihalf[d];
   }
@@ -1023,7 +1163,7 @@ __device__ __forceinline__ void pi_source(const FSet& u, const FSet& uE,
 
 // Scale pi~ so that sqrt(|pi~:pi~|) <= pi_reg (e+P); zero it where e+P = 0.
 // BK: Pi is clipped to [-P, P] and Pi, n are zero where e+P = 0 too.
-template <bool BK = false>
+template <bool FAST, bool BK>
 __device__ __forceinline__ void regulate(const EosDev& eos, const StepParams& p, double e,
                                          double* pv) {
   if (!(p.pi_reg > 0.0)) return;
@@ -1041,9 +1181,18 @@ __device__ __forceinline__ void regulate(const EosDev& eos, const StepParams& p,
   const double pp = pv[0] * pv[0] + pv[4] * pv[4] + pv[7] * pv[7] + pv[9] * pv[9] -
                     2.0 * (pv[1] * pv[1] + pv[2] * pv[2] + pv[3] * pv[3]) +
                     2.0 * (pv[5] * pv[5] + pv[6] * pv[6] + pv[8] * pv[8]);
-  const double rho = sqrt(fabs(pp)) / w;
-  if (rho > p.pi_reg) {
-    const double f = p.pi_reg / rho;
+  double f = 1.0;
+  bool over;
+  if constexpr (FAST) {
+    const double cap = p.pi_reg * w;
+    over = fabs(pp) > cap * cap;
+    if (over) f = cap * inv_root<true>(fabs(pp));
+  } else {
+    const double rho = sqrt(fabs(pp)) / w;
+    over = rho > p.pi_reg;
+    if (over) f = p.pi_reg / rho;
+  }
+  if (over) {
 #pragma unroll
     for (int m = 0; m < 10; ++m) pv[m] *= f;
   }
@@ -1176,7 +1325,7 @@ __global__ __launch_bounds__(kBlock) void k_init_conserved(Fields f, StepParams 
   const double x0 = root_guess<NET>(p, act, K0, K1, K2, K3, K0);
   if (!act) return;
   int it, fl;
-  const Prim s = con2prim(eos, p, K0, K1, K2, K3, x0, it, fl);
+  const Prim s = con2prim<false>(eos, p, K0, K1, K2, K3, x0, it, fl);
   f.e[c] = s.e;
   f.u[0][c] = s.u1;
   f.u[1][c] = s.u2;
@@ -1198,7 +1347,7 @@ __device__ __forceinline__ void first_estimate_cell(const DFields& f, const Step
     u1 = f.u[0][c];
     u2 = f.u[1][c];
     u3 = f.u[2][c];
-    const double ut = utau(u1, u2, u3);
+    const double ut = utau<false>(u1, u2, u3);
     double P, cs2;
     eos_p_cs2(eos, e, P, cs2);
     const double w = (e > 0.0 ? e : 0.0) + P;
@@ -1216,7 +1365,7 @@ __device__ __forceinline__ void first_estimate_cell(const DFields& f, const Step
   const double x0 = root_guess<false>(p, q.active, K[0], K[1], K[2], K[3], e);
   if (!q.active) return;
   int it, fl;
-  const Prim s = con2prim(eos, p, K[0], K[1], K[2], K[3], x0, it, fl);
+  const Prim s = con2prim<false>(eos, p, K[0], K[1], K[2], K[3], x0, it, fl);
   st_cell(f.up[0] + c, 2.0 * u1 - s.u1);
   st_cell(f.up[1] + c, 2.0 * u2 - s.u2);
   st_cell(f.up[2] + c, 2.0 * u3 - s.u3);
@@ -1273,7 +1422,7 @@ __device__ __forceinline__ void stage1_source(const DFields& f, const StepParams
     double e, u1, u2, u3, pc[NQ];
     cell_values<RT, VISC, NQ>(f, c, e, u1, u2, u3, pc);
     if (!g.cart) {  // geometric source S_T = (-Tc^{ee}, 0, 0, -Tc^{te})
-      const double ut = utau(u1, u2, u3);
+      const double ut = utau<kFast<RT>>(u1, u2, u3);
       double P, cs2;
       eos_p_cs2(eos, e, P, cs2);
       if constexpr (BK) P += pc[10];
@@ -1305,7 +1454,7 @@ __device__ __forceinline__ void stage1_cell(const DFields& f, const StepParams& 
     // the cell's values again (cache hits after the face rounds)
     double e, u1, u2, u3, pc[NQ];
     cell_values<RT, VISC, NQ>(f, c, e, u1, u2, u3, pc);
-    const double ut = utau(u1, u2, u3);
+    const double ut = utau<kFast<RT>>(u1, u2, u3);
     double p1[NQ];
     if (VISC) {
       // u* = 2u^n - u^{n-1}: not needed where pi~' is zero whatever it is
@@ -1316,11 +1465,11 @@ __device__ __forceinline__ void stage1_cell(const DFields& f, const StepParams& 
       if (!zero) {
         const double s1 = 2.0 * u1 - f.up[0][c], s2 = 2.0 * u2 - f.up[1][c],
                      s3 = 2.0 * u3 - f.up[2][c];
-        inv_uts = 1.0 / utau(s1, s2, s3);
+        inv_uts = inv_utau<kFast<RT>>(s1, s2, s3);
       }
 #pragma unroll
       for (int m = 0; m < NQ; ++m) p1[m] = (ut * pc[m] + p.h * R[4 + m]) * inv_uts;
-      regulate<BK>(eos, p, e, p1);
+      regulate<kFast<RT>, BK>(eos, p, e, p1);
       // with vac_zero, pi~' is zero where e^n is: stage 2pi reads it masked there
       if (!(KTMI_PI1_SPARSE && !BK && p.vac_zero && e == 0.0)) {
 #pragma unroll
@@ -1354,7 +1503,7 @@ __device__ __forceinline__ void stage1_asleep(const DFields& f, const StepParams
 }
 
 // Stage 1's root solve of K (all lanes of a wave call it), e' and u~' stored.
-template <bool NET, bool BK>
+template <typename RT, bool NET, bool BK>
 __device__ __forceinline__ void stage1_solve(const DFields& f, const StepParams& p,
                                              const EosDev& eos, const Pos& q, const double* K,
                                              double prev, double Pi1, CellDiag& v) {
@@ -1362,7 +1511,7 @@ __device__ __forceinline__ void stage1_solve(const DFields& f, const StepParams&
   if (q.active) {
     const int c = q.c;
     int it, fl;
-    const Prim s = con2prim<BK>(eos, p, K[0], K[1], K[2], K[3], x0, it, fl, Pi1);
+    const Prim s = con2prim<kFast<RT>, BK>(eos, p, K[0], K[1], K[2], K[3], x0, it, fl, Pi1);
     count_solve(v, it, fl);
     st_cell(f.e1 + c, s.e);
     st_cell(f.u1[0] + c, s.u1);
@@ -1426,7 +1575,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     for (int nu = 0; nu < 4; ++nu) st_cell(f.T1[nu] + q.c, T1[nu]);
   }
   if (threadIdx.x == 0) cx.t1same[cx.tile] = all_same;
-  stage1_solve<NET, BK>(f, p, eos, q, K, prev, Pi1, v);
+  stage1_solve<RT, NET, BK>(f, p, eos, q, K, prev, Pi1, v);
   block_partials(v, f.partial, cx.tg.ntiles, cx.tile, &shgeo);
 }
 
@@ -1480,9 +1629,9 @@ __device__ __forceinline__ bool stage2_pi_cell(const DFields& f, const StepParam
     if (!vz) {
       en = f.e[c];
       const double a1 = f.u[0][c], a2 = f.u[1][c], a3 = f.u[2][c];
-      const double utn = utau(a1, a2, a3);
-      const double uts = utau(2.0 * a1 - f.up[0][c], 2.0 * a2 - f.up[1][c], 2.0 * a3 - f.up[2][c]);
-      const double inv_ut1 = 1.0 / utau(f.u1[0][c], f.u1[1][c], f.u1[2][c]);
+      const double utn = utau<kFast<RT>>(a1, a2, a3);
+      const double uts = utau<kFast<RT>>(2.0 * a1 - f.up[0][c], 2.0 * a2 - f.up[1][c], 2.0 * a3 - f.up[2][c]);
+      const double inv_ut1 = inv_utau<kFast<RT>>(f.u1[0][c], f.u1[1][c], f.u1[2][c]);
       double pin[NQ];  // pi~^n, zero where e^n = 0
 #pragma unroll
       for (int m = 0; m < NQ; ++m) pin[m] = 0.0;
@@ -1493,7 +1642,7 @@ __device__ __forceinline__ bool stage2_pi_cell(const DFields& f, const StepParam
 #pragma unroll
       for (int m = 0; m < NQ; ++m)
         pn[m] = (0.5 * (utn * pin[m] + uts * pc[m]) + 0.5 * p.h * R[4 + m]) * inv_ut1;
-      regulate<BK>(eos, p, e1, pn);
+      regulate<kFast<RT>, BK>(eos, p, e1, pn);
     } else if (p.quiet_r[0] > 0) {
       en = f.e[c];
     }
@@ -1566,7 +1715,7 @@ __device__ __forceinline__ bool stage2_T_cell(const DFields& f, const StepParams
       eos_p_cs2(eos, e1, P, cs2);
       if constexpr (BK) P += PiN;
       const double w = (e1 > 0.0 ? e1 : 0.0) + P;
-      const double ut = utau(u1, u2, u3);
+      const double ut = utau<kFast<RT>>(u1, u2, u3);
       const double see = -(w * u3 * u3 + P + pc[9]);
       R[0] += see;
       R[3] += -(w * ut * u3 + pc[3]);
@@ -1601,7 +1750,7 @@ __device__ __forceinline__ bool stage2_T_cell(const DFields& f, const StepParams
   if (q.active) {
     const int c = q.c;
     int it, fl;
-    const Prim s = con2prim<BK>(eos, p, K[0], K[1], K[2], K[3], x0, it, fl, PiN);
+    const Prim s = con2prim<kFast<RT>, BK>(eos, p, K[0], K[1], K[2], K[3], x0, it, fl, PiN);
     count_solve(v, it, fl);
     if (p.quiet_r[0] > 0)  // e before and after stage 1 (viscous: tested in stage2pi)
       quiet = VISC || (f.e[c] == 0.0 && prev == 0.0);
@@ -1825,7 +1974,7 @@ __global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_stage1_sma
 #pragma unroll
     for (int nu = 0; nu < 4; ++nu) st_cell(f.T1[nu] + q.c, T1[nu]);
   }
-  stage1_solve<false, BK>(f, p, eos, q, K, prev, Pi1, v);
+  stage1_solve<RT, false, BK>(f, p, eos, q, K, prev, Pi1, v);
   small_partials(v, f.partial, cx.tg.ntiles, cx.tile);
 }
 

@@ -389,7 +389,8 @@ static int run_tile(const ktmi_handle* h, TileGrid* tg) {
 }
 
 // Doubles reserved for the per-tile flags: 4 ints per tile of the largest grid
-// (quiet flags by clock parity, the stage-2pi part, and stage 1's T~' = T~^n).
+// (quiet flags by clock parity, the stage-2pi part, and stage 1's T~' = T~^n, each with the
+// vacuum marks in its higher bits).
 static size_t quiet_doubles(const ktmi_desc* d) {
   return ((size_t)4 * max_tiles(d) + 63) / 64 * 32;
 }
@@ -586,7 +587,8 @@ static int enqueue_step(ktmi_handle* h) {
   });
 }
 
-// Marks every tile as not quiet (the next step computes them all).
+// Marks every tile as neither quiet nor known to be vacuum (the next step computes and tests
+// them all).
 static int clear_quiet(ktmi_handle* h) {
   if (!h->bound) return KTMI_OK;
   const int n = (int)quiet_doubles(&h->d);
@@ -599,6 +601,7 @@ static int clear_quiet(ktmi_handle* h) {
 static int finish_initial(ktmi_handle* h) {
   if (int rc = upload_event(h)) return rc;
   hipLaunchKernelGGL(k_set_clock, dim3(1), dim3(64), 0, h->stream, h->clock, h->tau);
+  if (int rc = clear_quiet(h)) return rc;  // before the first estimate, which leaves marks
   TileGrid tg;
   const int tile = run_tile(h, &tg);
   int rc = launch(h, K_FIRST, [&] {
@@ -609,7 +612,6 @@ static int finish_initial(ktmi_handle* h) {
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(kBlock), 0, h->stream, h->f.acc, 32);
   });
   if (rc) return rc;
-  if (int rc2 = clear_quiet(h)) return rc2;
   h->step = 0;
   h->ready = true;
   return KTMI_OK;
@@ -1209,7 +1211,7 @@ int ktmi_quiet_tiles(ktmi_handle* h, long* quiet, long* total) {
   HIP_TRY(h, hipMemcpyAsync(flags.data(), src, sizeof(int) * nt, hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   long n = 0;
-  for (int v : flags) n += v != 0;
+  for (int v : flags) n += v & 1;
   *quiet = n;
   *total = nt;
   return KTMI_OK;

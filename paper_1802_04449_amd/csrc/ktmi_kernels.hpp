@@ -64,8 +64,8 @@ struct Fields {
   double* T1[4];
   double* partial;  // [2][kNP][nblk]: stage1 then stage2T, slot-major
   double* acc;      // [16] accumulated diagnostics
-  int* quiet;       // [4][ntiles]: quiet flags by clock parity (2), stage-2pi part (1),
-                    // stage 1 T~' = T~^n (1)
+  int* quiet;       // [4][ntiles]: bit 0: quiet flags by clock parity (2), stage-2pi part (1),
+                    // stage 1 T~' = T~^n (1); bits 1-2: vacuum marks (of e, pi~ and e')
   long fstride;     // elements from one field to the next
   int pf32;         // the pi~ blocks (pi, pi1) hold FP32 values (mixed precision)
 };
@@ -174,10 +174,10 @@ struct Ctx {
   TileGrid tg;
   Geo g;
   int tile;  // tile index inside the event
-  const gint* qcur;  // quiet flags after the previous step
-  gint* qnext;       // quiet flags after this step
-  gint* qpi;         // this step's stage-2pi part of the flags
-  gint* t1same;      // this step's stage-1 flags: the tile's T~' equals T~^n (not stored)
+  gint* qcur;        // quiet flags and marks after the previous step
+  gint* qnext;       // quiet flags and marks after this step
+  gint* qpi;         // this step's stage-2pi part of the flags; kPiZeros
+  gint* t1same;      // this step's stage-1 flags: the tile's T~' equals T~^n (not stored); marks of e'
 };
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
@@ -317,9 +317,61 @@ __device__ __forceinline__ bool tile_asleep(const StepParams& p, const TileGrid&
   for (int n = threadIdx.x; n < wx * wy * wz; n += kBlock) {
     const int a = ti - rx + n / (wy * wz), b = tj - ry + (n / wz) % wy, c = tk - rz + n % wz;
     if (a < 0 || a >= tg.ntx || b < 0 || b >= tg.nty || c < 0 || c >= tg.ntz) continue;
-    awake |= qcur[(a * tg.nty + b) * tg.ntz + c] == 0;
+    awake |= (qcur[(a * tg.nty + b) * tg.ntz + c] & 1) == 0;
   }
   return __syncthreads_or(awake) == 0;
+}
+
+// x of lane l (wave-uniform).
+__device__ __forceinline__ int lane_of(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
+
+// Vacuum tiles.  Most of a heavy-ion grid is vacuum, and a tile of it has nothing to do but
+// carry a dilute T~; yet finding that out from the fields takes one or two dependent rounds
+// of loads and barriers per pass, and writing zeros over zeros the rest.  So the passes
+// leave a mark per tile in bits 1-2 of the tile flags: on e by stage 2T (beside the quiet
+// flags, by clock parity) and the first-step estimate, on e' by stage 1 (beside T~' = T~^n).
+// A tile whose marks and neighbours' marks (2 cells: the reach of a face stencil) all say
+// vacuum takes a short path that gives the same bits and stores only what is not there yet;
+// one marked as matter skips the test.  Cleared flags say nothing: the fields are tested.
+// us a pass (stage 1 / 2pi / 2T): 201x201x105 hotspots, 82% vacuum, 410/376/327 ->
+// 350/298/270, mixed 320/284/279 -> 293/228/225; 385x385x129 2254/2057/1658 ->
+// 1952/1626/1411; 101x99x65 without vacuum 170/150/114 -> 167/150/115.
+enum : int { kMarkNone = 0, kMarkVac = 1, kMarkVac2 = 2, kMarkMatter = 3 };
+__device__ __forceinline__ int mark_of(int flags) { return (flags >> 1) & 3; }
+// kPiZeros (stage 2pi's flag): pi~ of the whole tile is stored as zero.
+constexpr int kPiZeros = 2;
+
+// What the marks say of the box that the tile's face stencils read, wave-uniform; a second
+// field's marks (n2) have to agree.  Tiles too short for 64 lanes to hold their neighbours'
+// marks are never kBoxClear.
+enum : int { kBoxUnknown = 0, kBoxOwnVac, kBoxMatter, kBoxClear };
+template <int TX, int TY, int TZ, bool TWO>
+__device__ __forceinline__ int box_marks(const TileGrid& tg, const gint* n1, const gint* n2,
+                                         int tile) {
+  constexpr int rx = (TX + 1) / TX, ry = (TY + 1) / TY, rz = (TZ + 1) / TZ;
+  constexpr int wx = 2 * rx + 1, wy = 2 * ry + 1, wz = 2 * rz + 1;
+  constexpr bool FIT = wx * wy * wz <= 64;
+  constexpr int OWN = FIT ? (rx * wy + ry) * wz + rz : 0;
+  const int n = threadIdx.x & 63;
+  int m1 = kMarkVac, m2 = kMarkVac;
+  if (FIT) {
+    const int tk = tile % tg.ntz, r = tile / tg.ntz;
+    const int tj = r % tg.nty, ti = r / tg.nty;
+    const int a = ti - rx + n / (wy * wz), b = tj - ry + (n / wz) % wy, c = tk - rz + n % wz;
+    if (n < wx * wy * wz && a >= 0 && a < tg.ntx && b >= 0 && b < tg.nty && c >= 0 && c < tg.ntz) {
+      const int t = (a * tg.nty + b) * tg.ntz + c;
+      m1 = mark_of(n1[t]);
+      if (TWO) m2 = mark_of(n2[t]);
+    }
+  } else {
+    m1 = mark_of(n1[tile]);
+    if (TWO) m2 = mark_of(n2[tile]);
+  }
+  const bool vac = (m1 == kMarkVac || m1 == kMarkVac2) && (m2 == kMarkVac || m2 == kMarkVac2);
+  if (FIT && __ballot(!vac) == 0) return kBoxClear;
+  const int o1 = lane_of(m1, OWN), o2 = lane_of(m2, OWN);
+  if (o1 == kMarkMatter || (TWO && o2 == kMarkMatter)) return kBoxMatter;
+  return o1 != kMarkNone ? kBoxOwnVac : kBoxUnknown;
 }
 
 // Max over the tile's faces of c / Delta when every face is a vacuum face.
@@ -750,7 +802,8 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
                                                   const FSet& u, const FSet& pi,
                                                   const StepParams& p, const EosDev& eos,
                                                   double tauf, const Pos& q, double* R,
-                                                  RT* lds, GField ez = GField{nullptr}) {
+                                                  RT* lds, GField ez = GField{nullptr},
+                                                  int box = kBoxUnknown) {
   constexpr int N = TX * TY * TZ;
   constexpr int NQ = BK ? 12 : 10, NC = 4 + NQ;
   if constexpr (ZERO_R) {
@@ -770,12 +823,15 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
 #ifndef KTMI_S1_TILE_TEST
 #define KTMI_S1_TILE_TEST 1
 #endif
-  if (PI_SRC == 2 || KTMI_S1_TILE_TEST) {
+  if ((PI_SRC == 2 || KTMI_S1_TILE_TEST) && box != kBoxMatter) {
     constexpr int BX = TX + 4, BY = TY + 4, BZ = TZ + 4, NB = BX * BY * BZ;
     // the tile's own cells first (one load per thread, which the cell phase
     // reuses): a tile with matter skips the rest of the test
-    int nz = q.active && e[q.c] != 0.0;
-    int any = __syncthreads_or(nz);
+    int nz = 0, any = 0;
+    if (box != kBoxOwnVac) {
+      nz = q.active && e[q.c] != 0.0;
+      any = __syncthreads_or(nz);
+    }
     if (!any) {
       for (int b = tid; b < NB; b += kBlock) {
         const int bx = b / (BY * BZ), by = (b / BZ) % BY, bz = b % BZ;
@@ -1224,7 +1280,6 @@ template <int CTRL>
 __device__ __forceinline__ double dpp(double x) {
   return __hiloint2double(dpp<CTRL>(__double2hiint(x)), dpp<CTRL>(__double2loint(x)));
 }
-__device__ __forceinline__ int lane_of(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
 __device__ __forceinline__ double lane_of(double x, int l) {
   return __hiloint2double(lane_of(__double2hiint(x), l), lane_of(__double2loint(x), l));
 }
@@ -1282,9 +1337,12 @@ __device__ __forceinline__ void fold_geo(double geo, GeoWaves& sh) {
 }
 
 // The workgroup's partials: its waves in order.
-__device__ __forceinline__ void block_partials(const CellDiag& d, gdouble* out, int ntiles,
-                                               int tile, const GeoWaves* geo = nullptr) {
+// Returns whether `matter` holds in any thread.
+__device__ __forceinline__ bool block_partials(const CellDiag& d, gdouble* out, int ntiles,
+                                               int tile, const GeoWaves* geo = nullptr,
+                                               bool matter = false) {
   __shared__ double red[kBlock / 64][kNP];
+  __shared__ int some[kBlock / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double v[kNP];
   wave_partials(d, v);
@@ -1292,6 +1350,8 @@ __device__ __forceinline__ void block_partials(const CellDiag& d, gdouble* out, 
 #pragma unroll
     for (int s = 0; s < kNP; ++s) red[wave][s] = geo && s == P_GEO ? geo->w[wave] : v[s];
   }
+  const bool any = __ballot(matter) != 0;
+  if (lane == 0) some[wave] = any;
   __syncthreads();
   if (threadIdx.x < kNP) {
     const int s = threadIdx.x;
@@ -1299,11 +1359,20 @@ __device__ __forceinline__ void block_partials(const CellDiag& d, gdouble* out, 
     for (int w = 1; w < kBlock / 64; ++w) x = is_max_slot(s) ? fmax(x, red[w][s]) : x + red[w][s];
     out[(size_t)s * ntiles + tile] = x;  // slot-major: the reduce reads coalesced
   }
+  int x = 0;
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; ++w) x |= some[w];
+  return x != 0;
 }
 
 // ---------------------------------------------------------------------------
 // Kernels
 // ---------------------------------------------------------------------------
+
+__device__ __forceinline__ bool zero_bits(const Prim& s) {
+  auto b = [](double x) { return __builtin_bit_cast(long long, x); };
+  return (b(s.e) | b(s.u1) | b(s.u2) | b(s.u3)) == 0;
+}
 
 // Initial conserved state: root solve of K = T~/tau0 - pi~^{tau .} from E.
 template <bool NET>
@@ -1338,7 +1407,7 @@ __global__ __launch_bounds__(kBlock) void k_init_conserved(Fields f, StepParams 
 // forward-Euler step of T~, the root solve, u~^{-1}.
 __device__ __forceinline__ void first_estimate_cell(const DFields& f, const StepParams& p,
                                                     const EosDev& eos, const Geo& g, const Pos& q,
-                                                    double* R) {
+                                                    double* R, bool& matter) {
   const double tf = g.cart ? 1.0 : g.tau;
   const int c = q.c;
   double K[4] = {1.0, 0.0, 0.0, 0.0}, e = 0.0, u1 = 0.0, u2 = 0.0, u3 = 0.0;
@@ -1363,6 +1432,7 @@ __device__ __forceinline__ void first_estimate_cell(const DFields& f, const Step
   }
   // the current e is a close start; the network is not used here
   const double x0 = root_guess<false>(p, q.active, K[0], K[1], K[2], K[3], e);
+  matter = q.active && !zero_bits(Prim{e, u1, u2, u3});
   if (!q.active) return;
   int it, fl;
   const Prim s = con2prim<false>(eos, p, K[0], K[1], K[2], K[3], x0, it, fl);
@@ -1385,7 +1455,10 @@ __global__ __launch_bounds__(kBlock) void k_first_estimate(const EventDesc* __re
   const double tf = g.cart ? 1.0 : g.tau;
   double R[14];
   tile_divergence<RT, TX, TY, TZ, true, false, 0>(f.e, f.u, f.pi, p, eos, tf, q, R, lds);
-  first_estimate_cell(f, p, eos, g, q, R);
+  bool matter;
+  first_estimate_cell(f, p, eos, g, q, R, matter);
+  const int any = __syncthreads_or(matter);
+  if (threadIdx.x == 0) cx.qcur[cx.tile] = (any ? kMarkMatter : kMarkVac) << 1;
 }
 
 // A cell's e, u~ and (VISC) pi~ at the current level; u~ and pi~ read as zero
@@ -1502,21 +1575,51 @@ __device__ __forceinline__ void stage1_asleep(const DFields& f, const StepParams
   if (q.active) v.fl = f.T[0][q.c] < 0.0 ? kNeg : 0;
 }
 
-// Stage 1's root solve of K (all lanes of a wave call it), e' and u~' stored.
+// Stage 1's root solve of K (all lanes of a wave call it), e' and u~' stored (stored: zeros
+// are there already).  Returns whether the cell has matter.
 template <typename RT, bool NET, bool BK>
-__device__ __forceinline__ void stage1_solve(const DFields& f, const StepParams& p,
+__device__ __forceinline__ bool stage1_solve(const DFields& f, const StepParams& p,
                                              const EosDev& eos, const Pos& q, const double* K,
-                                             double prev, double Pi1, CellDiag& v) {
+                                             double prev, double Pi1, CellDiag& v,
+                                             bool stored = false) {
   const double x0 = root_guess<NET>(p, q.active, K[0], K[1], K[2], K[3], prev);
+  bool matter = false;
   if (q.active) {
     const int c = q.c;
     int it, fl;
     const Prim s = con2prim<kFast<RT>, BK>(eos, p, K[0], K[1], K[2], K[3], x0, it, fl, Pi1);
     count_solve(v, it, fl);
+    matter = !zero_bits(s);
+    if (stored && !matter) return false;
     st_cell(f.e1 + c, s.e);
     st_cell(f.u1[0] + c, s.u1);
     st_cell(f.u1[1] + c, s.u2);
     st_cell(f.u1[2] + c, s.u3);
+  }
+  return matter;
+}
+
+// Stage 1 of a cell whose tile's box is vacuum (kBoxClear): no flux and no source (P(0) = 0),
+// so T~' = T~^n up to the sign of a zero, and pi~' = 0 (stored only where stage 2pi would
+// read it, unless the step before left it there).
+template <typename RT, bool VISC, bool BK>
+__device__ __forceinline__ void stage1_cell_clear(const DFields& f, const StepParams& p,
+                                                  const Geo& g, const Pos& q, double* K, double* T1,
+                                                  bool& t1same, bool pi1_stored) {
+  if (!q.active) return;
+#pragma unroll
+  for (int nu = 0; nu < 4; ++nu) {
+    const double t0 = f.T[nu][q.c];
+    // the geometric source of e = 0 is -0
+    T1[nu] = t0 + (!g.cart && (nu == 0 || nu == 3) ? -0.0 : 0.0);
+    t1same = t1same && __builtin_bit_cast(long long, T1[nu]) == __builtin_bit_cast(long long, t0);
+  }
+  const double inv_tf1 = 1.0 / (g.cart ? 1.0 : g.tau1);
+#pragma unroll
+  for (int nu = 0; nu < 4; ++nu) K[nu] = T1[nu] * inv_tf1;
+  if (VISC && (BK || !KTMI_PI1_SPARSE) && !pi1_stored) {
+#pragma unroll
+    for (int m = 0; m < (BK ? 12 : 10); ++m) stq<RT>(f.pi1[m], q.c, 0.0);
   }
 }
 
@@ -1551,6 +1654,27 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     block_partials(v, f.partial, cx.tg.ntiles, cx.tile);
     return;
   }
+  const int box = box_marks<TX, TY, TZ, false>(cx.tg, cx.qcur, nullptr, cx.tile);
+  double K[4] = {1.0, 0.0, 0.0, 0.0}, prev = 0.0, Pi1 = 0.0;
+  double T1[4];
+  bool t1same = true;  // T~' = T~^n bitwise in this cell (no flux or source)
+  const bool clear = box == kBoxClear && p.vac_zero;
+  if (clear) {
+    const int own = cx.t1same[cx.tile];
+    v.cfl = vacuum_cfl<RT>(p, tf) * p.h;
+    stage1_cell_clear<RT, VISC, BK>(f, p, g, q, K, T1, t1same,
+                                    mark_of(cx.qcur[cx.tile]) == kMarkVac2);
+    const int all_same = __syncthreads_and(t1same);
+    if (!all_same && q.active) {
+#pragma unroll
+      for (int nu = 0; nu < 4; ++nu) st_cell(f.T1[nu] + q.c, T1[nu]);
+    }
+    const bool m = stage1_solve<RT, NET, BK>(f, p, eos, q, K, 0.0, 0.0, v, mark_of(own) == kMarkVac);
+    const bool any = block_partials(v, f.partial, cx.tg.ntiles, cx.tile, nullptr, m);
+    const int now = (any ? kMarkMatter : kMarkVac) << 1 | (all_same ? 1 : 0);
+    if (threadIdx.x == 0 && now != own) cx.t1same[cx.tile] = now;
+    return;
+  }
   double R[4 + NQ];
 #pragma unroll
   for (int k = 0; k < 4 + NQ; ++k) R[k] = 0.0;
@@ -1560,11 +1684,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
   stage1_source<RT, VISC, L1, BK>(f, p, eos, g, q, R, geo);
   fold_geo(geo, shgeo);
   const double cfl = tile_divergence<RT, TX, TY, TZ, true, VISC, VISC ? 1 : 0, BK, true, false,
-                                     false>(f.e, f.u, f.pi, p, eos, tf, q, R, lds);
+                                     false>(f.e, f.u, f.pi, p, eos, tf, q, R, lds,
+                                            GField{nullptr}, box);
   v.cfl = cfl * p.h;
-  double K[4] = {1.0, 0.0, 0.0, 0.0}, prev = 0.0, Pi1 = 0.0;
-  double T1[4];
-  bool t1same = true;  // T~' = T~^n bitwise in this cell (no flux or source)
   stage1_cell<RT, VISC, BK>(f, p, eos, g, q, R, K, T1, t1same, prev, Pi1);
   // A tile whose T~' equals T~^n in every cell (a vacuum tile: no flux, no
   // source) does not store it; stage 2T reads T~^n for it instead (the flag is
@@ -1574,9 +1696,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
     for (int nu = 0; nu < 4; ++nu) st_cell(f.T1[nu] + q.c, T1[nu]);
   }
-  if (threadIdx.x == 0) cx.t1same[cx.tile] = all_same;
-  stage1_solve<RT, NET, BK>(f, p, eos, q, K, prev, Pi1, v);
-  block_partials(v, f.partial, cx.tg.ntiles, cx.tile, &shgeo);
+  const bool m = stage1_solve<RT, NET, BK>(f, p, eos, q, K, prev, Pi1, v);
+  const bool any = block_partials(v, f.partial, cx.tg.ntiles, cx.tile, &shgeo, m);
+  if (threadIdx.x == 0)
+    cx.t1same[cx.tile] = (any ? kMarkMatter : kMarkVac) << 1 | (all_same ? 1 : 0);
 }
 
 // Stage 2pi's relaxation source of the thread's cell into R[4...].  Where e' = 0 the
@@ -1674,6 +1797,20 @@ __attribute__((amdgpu_waves_per_eu(pi_waves<RT, TX, TY, TZ, BK, BK ? 16 : 14>())
   const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile, threadIdx.x);
   if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) return;
   const double tf = g.cart ? 1.0 : g.tau;
+  const int box = box_marks<TX, TY, TZ, true>(cx.tg, cx.t1same, cx.qcur, cx.tile);
+  const int own = cx.qpi[cx.tile];
+  if (box == kBoxClear && p.vac_zero) {  // pi^{n+1} = 0; pi~' is too, so the tile is quiet
+    if (!(own & kPiZeros)) {
+      if (q.active) {
+#pragma unroll
+        for (int m = 0; m < NQ; ++m) stq<RT>(f.pi[m], q.c, 0.0);
+      }
+      __syncthreads();  // every wave has read the flag
+    }
+    const int now = kPiZeros | (p.quiet_r[0] > 0 ? 1 : 0);
+    if (threadIdx.x == 0 && now != own) cx.qpi[cx.tile] = now;
+    return;
+  }
   double R[4 + NQ];
 #pragma unroll
   for (int k = 0; k < 4 + NQ; ++k) R[k] = 0.0;
@@ -1681,36 +1818,48 @@ __attribute__((amdgpu_waves_per_eu(pi_waves<RT, TX, TY, TZ, BK, BK ? 16 : 14>())
   stage2_pi_source<RT, L1, BK>(f, p, eos, g, q, R);
   // pi~' was regulated with e^n in stage 1: zero wherever e^n is (vac_zero)
   tile_divergence<RT, TX, TY, TZ, false, true, 2, BK, false, false, false>(
-      f.e1, f.u1, f.pi1, p, eos, tf, q, R, lds, f.e);
+      f.e1, f.u1, f.pi1, p, eos, tf, q, R, lds, f.e, box);
   const bool quiet = stage2_pi_cell<RT, BK>(f, p, eos, q, R);
   if (p.quiet_r[0] > 0) {
     const int all = __syncthreads_and(quiet);
-    if (threadIdx.x == 0) cx.qpi[cx.tile] = all;
+    if (threadIdx.x == 0) cx.qpi[cx.tile] = all ? 1 : 0;
+  } else if (own != 0) {  // (own == 0 unless the tile was vacuum)
+    __syncthreads();
+    if (threadIdx.x == 0) cx.qpi[cx.tile] = 0;
   }
 }
 
 // Stage 2T's corrector of the thread's cell from its divergence R: T~^{n+1} (t1s: T~' was
 // left unstored, equal to T~^n), the root solve, (e, u~)^{n+1} stored.  All lanes of a wave
-// call it.  Returns the cell's part of the quiet-tile test.
-template <typename RT, bool VISC, bool BK>
+// call it.  CLEAR: the tile's box is vacuum in e', so no flux, source or pi~; mark: the tile's
+// mark for e^n, which says which zeros are stored already.  Returns the cell's part of the
+// quiet-tile test; matter: whether the new state is not vacuum.
+template <typename RT, bool VISC, bool BK, bool CLEAR>
 __device__ __forceinline__ bool stage2_T_cell(const DFields& f, const StepParams& p,
                                               const EosDev& eos, const Geo& g, const Pos& q,
-                                              double* R, bool t1s, CellDiag& v) {
+                                              double* R, bool t1s, CellDiag& v, bool& matter,
+                                              int mark) {
   constexpr int NT = BK ? 11 : 10;  // the components T~ uses: pi~ (and Pi)
   double K[4] = {1.0, 0.0, 0.0, 0.0}, prev = 0.0, PiN = 0.0;
   if (q.active) {
     const int c = q.c;
-    const double e1 = f.e1[c], u1 = f.u1[0][c], u2 = f.u1[1][c], u3 = f.u1[2][c];
+    double e1 = 0.0, u1 = 0.0, u2 = 0.0, u3 = 0.0;
+    if (!CLEAR) {
+      e1 = f.e1[c];
+      u1 = f.u1[0][c];
+      u2 = f.u1[1][c];
+      u3 = f.u1[2][c];
+    }
     // where e' = 0 the regulator zeroed pi^{n+1} in stage 2pi (vac_zero): no loads
     double pc[NT];
 #pragma unroll
     for (int m = 0; m < NT; ++m) pc[m] = 0.0;
-    if (VISC && !(e1 == 0.0 && p.vac_zero)) {
+    if (VISC && !CLEAR && !(e1 == 0.0 && p.vac_zero)) {
 #pragma unroll
       for (int m = 0; m < NT; ++m) pc[m] = ldq<RT>(f.pi[m], c);
     }
     if constexpr (BK) PiN = pc[10];
-    if (!g.cart) {
+    if (!CLEAR && !g.cart) {  // (P(0) = 0: no source in the vacuum)
       double P, cs2;
       eos_p_cs2(eos, e1, P, cs2);
       if constexpr (BK) P += PiN;
@@ -1727,9 +1876,9 @@ __device__ __forceinline__ bool stage2_T_cell(const DFields& f, const StepParams
       const double t0 = f.T[nu][c];
       // stage 1 left T~' = T~^n unstored in such a tile: the loaded value is
       // stale there and replaced (loading it anyway keeps the loads together)
-      const double t1l = f.T1[nu][c];
+      const double t1l = CLEAR && t1s ? t0 : f.T1[nu][c];
       const double t1 = t1s ? t0 : t1l;
-      Tn[nu] = t0 + 0.5 * ((t1 - t0) + p.h * R[nu]);
+      Tn[nu] = t0 + 0.5 * ((t1 - t0) + (CLEAR ? 0.0 : p.h * R[nu]));
       // T~^{n+1} goes over T~^n: a value that is bitwise unchanged (a vacuum
       // tile's cells, where no flux or source acts) is already in memory
       if (__builtin_bit_cast(long long, Tn[nu]) != __builtin_bit_cast(long long, t0))
@@ -1746,6 +1895,7 @@ __device__ __forceinline__ bool stage2_T_cell(const DFields& f, const StepParams
   // 64-event batch the network here cost 3% of the step and 0.004 iterations per
   // solve more than e')
   const double x0 = root_guess<false>(p, q.active, K[0], K[1], K[2], K[3], prev);
+  matter = false;
   bool quiet = true;  // this cell's part of the quiet-tile test
   if (q.active) {
     const int c = q.c;
@@ -1755,10 +1905,14 @@ __device__ __forceinline__ bool stage2_T_cell(const DFields& f, const StepParams
     if (p.quiet_r[0] > 0)  // e before and after stage 1 (viscous: tested in stage2pi)
       quiet = VISC || (f.e[c] == 0.0 && prev == 0.0);
     quiet = quiet && s.e == 0.0 && !(K[0] >= p.eps_cut);
-    st_cell(f.e + c, s.e);
-    st_cell(f.up[0] + c, s.u1);  // becomes u~^{n+1} after the host swaps u and up
-    st_cell(f.up[1] + c, s.u2);
-    st_cell(f.up[2] + c, s.u3);
+    matter = !zero_bits(s);
+    // CLEAR: zeros that a vacuum e^n (and u~^{n-1}, kMarkVac2) left are not written again
+    if (!(CLEAR && !matter && (mark == kMarkVac || mark == kMarkVac2))) st_cell(f.e + c, s.e);
+    if (!(CLEAR && !matter && mark == kMarkVac2)) {
+      st_cell(f.up[0] + c, s.u1);  // becomes u~^{n+1} after the host swaps u and up
+      st_cell(f.up[1] + c, s.u2);
+      st_cell(f.up[2] + c, s.u3);
+    }
     v.emax = s.e;
     if (s.e == 0.0) v.fl |= kVacAfter;
   }
@@ -1793,23 +1947,35 @@ __attribute__((amdgpu_waves_per_eu(s2t_waves<RT, TX, TY, TZ, BK>()))) void k_sta
   const Pos q = cell_pos<TX, TY, TZ>(p, cx.tg, cx.tile, threadIdx.x);
   CellDiag v;
   const double tf = g.cart ? 1.0 : g.tau;
+  const int own = cx.qcur[cx.tile];
   if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) {
     stage2_T_asleep<RT>(f, p, q, tf, v);
     block_partials(v, f.partial + (size_t)kNP * cx.tg.ntiles, cx.tg.ntiles, cx.tile);
-    if (threadIdx.x == 0) cx.qnext[cx.tile] = 1;
+    if (threadIdx.x == 0) cx.qnext[cx.tile] = own | 1;
     return;
   }
-  double R[BK ? 16 : 14];
-  const double cfl = tile_divergence<RT, TX, TY, TZ, true, false, VISC ? 2 : 0, BK, false, true>(
-      f.e1, f.u1, f.pi, p, eos, tf, q, R, lds);
-  v.cfl = cfl * p.h;
-  const bool t1s = cx.t1same[cx.tile] != 0;
-  const bool quiet = stage2_T_cell<RT, VISC, BK>(f, p, eos, g, q, R, t1s, v);
-  if (p.quiet_r[0] > 0) {
-    const int all = __syncthreads_and(quiet);
-    if (threadIdx.x == 0) cx.qnext[cx.tile] = all && (!VISC || cx.qpi[cx.tile]);
+  const int box = box_marks<TX, TY, TZ, false>(cx.tg, cx.t1same, nullptr, cx.tile);
+  const bool t1s = (cx.t1same[cx.tile] & 1) != 0;
+  const int mark = mark_of(own);  // of e^n
+  bool matter, quiet;
+  if (box == kBoxClear && p.vac_zero) {
+    v.cfl = vacuum_cfl<RT>(p, tf) * p.h;
+    quiet = stage2_T_cell<RT, VISC, BK, true>(f, p, eos, g, q, nullptr, t1s, v, matter, mark);
+  } else {
+    double R[BK ? 16 : 14];
+    const double cfl = tile_divergence<RT, TX, TY, TZ, true, false, VISC ? 2 : 0, BK, false, true>(
+        f.e1, f.u1, f.pi, p, eos, tf, q, R, lds, GField{nullptr}, box);
+    v.cfl = cfl * p.h;
+    quiet = stage2_T_cell<RT, VISC, BK, false>(f, p, eos, g, q, R, t1s, v, matter, mark);
   }
-  block_partials(v, f.partial + (size_t)kNP * cx.tg.ntiles, cx.tg.ntiles, cx.tile);
+  int all = 0;
+  if (p.quiet_r[0] > 0) all = __syncthreads_and(quiet) && (!VISC || (cx.qpi[cx.tile] & 1));
+  const bool any =
+      block_partials(v, f.partial + (size_t)kNP * cx.tg.ntiles, cx.tg.ntiles, cx.tile, nullptr, matter);
+  if (threadIdx.x == 0) {
+    const int now = any ? kMarkMatter : (mark == kMarkVac || mark == kMarkVac2 ? kMarkVac2 : kMarkVac);
+    cx.qnext[cx.tile] = now << 1 | (all ? 1 : 0);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1939,7 +2105,8 @@ __global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_first_esti
   __syncthreads();
   if (wave < AXES) return;
   small_divergence<RT, TX, TY, TZ, true, false, false>(lds, p, tf, q, R);
-  first_estimate_cell(f, p, eos, g, q, R);
+  bool matter;  // (these kernels leave no marks)
+  first_estimate_cell(f, p, eos, g, q, R, matter);
 }
 
 template <typename RT, int TX, int TY, int TZ, bool VISC, bool L1, bool BK = false>
@@ -2026,7 +2193,9 @@ __global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_stage2_T_s
                                                                      wave, lane, lds) * p.h;
   if (small_handover<AXES>(wave, cfl, shcfl, v)) return;
   small_divergence<RT, TX, TY, TZ, true, false, BK>(lds, p, tf, q, R);
-  const bool quiet = stage2_T_cell<RT, VISC, BK>(f, p, eos, g, q, R, false, v);
+  bool matter;
+  const bool quiet = stage2_T_cell<RT, VISC, BK, false>(f, p, eos, g, q, R, false, v, matter,
+                                                        kMarkNone);
   if (p.quiet_r[0] > 0) {
     const int all = __ballot(!quiet) == 0;
     if (lane == 0) cx.qnext[cx.tile] = all && (!VISC || cx.qpi[cx.tile]);

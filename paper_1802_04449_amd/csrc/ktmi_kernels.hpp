@@ -447,7 +447,7 @@ struct StencilIdx {
 // a-1 .. a+2 (generalized minmod with theta; zero-gradient boundaries by index
 // clamping).  Q_T = tau Tc^{tau nu}, F_T = tau Tc^{axis nu}; Q_pi = u~^tau
 // pi~, F_pi = u~^axis pi~; c = max local speed of the two face states.  The
-// components the pass uses (T~'s if DO_T, pi~'s if DO_PI) go to out[k * F];
+// components the pass uses (T~'s if DO_T, pi~'s if DO_PI), packed, go to out[k * F];
 // returns c.  BK: the transported set also holds the bulk pressure Pi (k = 14),
 // which adds to P in T~'s Q and F (eqn. Pitilde), and the net-baryon density n
 // (k = 15); both have the flux form of the pi~ components.
@@ -466,7 +466,7 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
   StencilIdx<FL::OFF32> ix;
 #pragma unroll
   for (int t = 0; t < 4; ++t) ix.set(t, base + clampi(a - 1 + t, 0, n - 1) * stride);
-  constexpr int NQ = BK ? 12 : 10;
+  constexpr int NQ = BK ? 12 : 10, K0 = DO_T ? 0 : 4;  // K0: first component in out
   constexpr bool F64 = sizeof(R) == 8;
   // Vacuum faces: every state the kernels write has u~ = 0 where e = 0, and
   // pi~ reads as zero there (PI_SRC 0/1; as stored in stage 2T, whose pi^{n+1}
@@ -499,7 +499,7 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
   if (vac && (PI_SRC != 2 || p.vac_zero)) {
 #pragma unroll
     for (int k = 0; k < 4 + NQ; ++k)
-      if (k < 4 ? DO_T : DO_PI) out[k * F] = R(0);
+      if (k < 4 ? DO_T : DO_PI) out[(k - K0) * F] = R(0);
     return (R)p.c_vac;
   }
   const R th = (R)p.theta;
@@ -623,7 +623,7 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
     }
   };
   if constexpr (BK) {
-    if (DO_PI) out[14 * F] = flux(fL[4], fR[4]);  // Pi's own flux
+    if (DO_PI) out[(14 - K0) * F] = flux(fL[4], fR[4]);  // Pi's own flux
   }
   // pi~ components (and n), one at a time; the loads of the component PF places on are
   // issued before the current one is used, so round trips to the caches overlap the
@@ -638,7 +638,7 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
   }
   if constexpr (DO_PI && NN == 0) {  // no pi~ (ideal)
 #pragma unroll
-    for (int m = 0; m < NQ; ++m) out[(4 + m) * F] = R(0);
+    for (int m = 0; m < NQ; ++m) out[(4 + m - K0) * F] = R(0);
   }
   if constexpr (WALK) {
 #pragma unroll
@@ -686,7 +686,7 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
       for (int t = 0; t < 4; ++t) p4[t] = (R)pc[t];
       const R pL = p4[1] + R(0.5) * mm_slope_r<R>(th, p4[0], p4[1], p4[2]);
       const R pR = p4[2] - R(0.5) * mm_slope_r<R>(th, p4[1], p4[2], p4[3]);
-      if (DO_PI) out[(4 + m) * F] = flux(pL, pR);
+      if (DO_PI) out[(4 + m - K0) * F] = flux(pL, pR);
       if constexpr (DO_T) {
 #pragma unroll
         for (int nu = 0; nu < 4; ++nu) {
@@ -726,12 +726,12 @@ __device__ __forceinline__ R face_flux_stream(const GField& e, const FSet& u,
 // the three axes are evaluated together in one round (their own LDS area), so a
 // 4x4x16 tile takes 4 rounds of face evaluations (144 remainder faces, then 256
 // per axis) instead of 6 in which every axis' second round keeps one wave busy.
-// Measured on the 201x201x105 grids this speeds up stage 1 by 5-13%; stage 2pi
-// gains on a grid without vacuum but loses up to 30% on the hotspot grid, where
-// most of its faces are vacuum faces loaded in full and rounds that mix axes cost
-// more (also with a window of x and y faces that adds no code), so the layout is
-// chosen per pass: SPLIT = false puts every face in full rounds (M_d = F_d, no
-// remainder).
+// Stage 1 and stage 2pi (5-13% of stage 1; us a pass of stage 2pi with only its own 10
+// components in LDS: 201x201x105 hotspots 297 -> 285, mixed 229 -> 219, 385x385x129 1611 ->
+// 1544, without vacuum 149 -> 140).  SPLIT = false puts every face in full rounds
+// (M_d = F_d, no remainder): the first-step estimate, once a run.
+// (The low faces of a wave's own cells in the full rounds, so that y and eta need no
+// barrier: stage 1 -2%, mixed +1.5%, stage 2pi +1%, mixed -1.5%: not kept.)
 template <int TX, int TY, int TZ, bool SPLIT = true>
 struct FaceLayout {
   static constexpr int N = TX * TY * TZ;
@@ -752,7 +752,7 @@ __device__ __forceinline__ double eval_face(const GField& e, const FSet& u,
                                             const FSet& pi, const StepParams& p,
                                             const EosDev& eos, double tauf, const Pos& q, int d,
                                             int f, RT* out, int S, GField ez = GField{nullptr}) {
-  constexpr int NC = BK ? 16 : 14;
+  constexpr int NC = BK ? 16 : 14, K0 = DO_T ? 0 : 4;
   const int nd = d == 0 ? p.nx : (d == 1 ? p.ny : p.ne);
   const double inv_del = d == 0 ? p.inv_dx : (d == 1 ? p.inv_dy : p.inv_de / tauf);
   const int stride = d == 0 ? p.ny * p.ne : (d == 1 ? p.ne : 1);
@@ -784,7 +784,7 @@ __device__ __forceinline__ double eval_face(const GField& e, const FSet& u,
   }
 #pragma unroll
   for (int k = 0; k < NC; ++k)
-    if (k < 4 ? DO_T : DO_PI) out[k * S] = RT(0);
+    if (k < 4 ? DO_T : DO_PI) out[(k - K0) * S] = RT(0);
   return 0.0;
 }
 
@@ -806,6 +806,8 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
                                                   int box = kBoxUnknown) {
   constexpr int N = TX * TY * TZ;
   constexpr int NQ = BK ? 12 : 10, NC = 4 + NQ;
+  // components in LDS: those the pass evaluates, from K0 on
+  constexpr int K0 = DO_T ? 0 : 4, NE = (DO_PI ? NC : 4) - K0;
   if constexpr (ZERO_R) {
 #pragma unroll
     for (int k = 0; k < NC; ++k) R[k] = 0.0;
@@ -907,24 +909,25 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
     __syncthreads();
   } else if constexpr (SPLIT) {
     using L = FaceLayout<TX, TY, TZ, SPLIT>;
-    RT* const rem = lds + NC * L::MMAX;  // remainder faces, axis after axis
+    RT* const rem = lds + NE * L::MMAX;  // remainder faces, axis after axis
     // Remainder round: the last R_d faces of every axis, one per thread.
     if constexpr (L::RSUM > 0) {
       if (tid < L::R0) {
         if (p.nx > 1)
           cfl = fmax(cfl, eval_face<RT, TX, TY, TZ, DO_T, DO_PI, PI_SRC, BK>(
-                              e, u, pi, p, eos, tauf, q, 0, L::M0 + tid, rem + tid, L::R0));
+                              e, u, pi, p, eos, tauf, q, 0, L::M0 + tid, rem + tid, L::R0, ez));
       } else if (tid < L::R0 + L::R1) {
         const int t = tid - L::R0;
         if (p.ny > 1)
           cfl = fmax(cfl, eval_face<RT, TX, TY, TZ, DO_T, DO_PI, PI_SRC, BK>(
-                              e, u, pi, p, eos, tauf, q, 1, L::M1 + t, rem + NC * L::R0 + t, L::R1));
+                              e, u, pi, p, eos, tauf, q, 1, L::M1 + t, rem + NE * L::R0 + t, L::R1,
+                              ez));
       } else if (tid < L::RSUM) {
         const int t = tid - L::R0 - L::R1;
         if (p.ne > 1)
           cfl = fmax(cfl, eval_face<RT, TX, TY, TZ, DO_T, DO_PI, PI_SRC, BK>(
                               e, u, pi, p, eos, tauf, q, 2, L::M2 + t,
-                              rem + NC * (L::R0 + L::R1) + t, L::R2));
+                              rem + NE * (L::R0 + L::R1) + t, L::R2, ez));
       }
     }
   #pragma unroll
@@ -933,10 +936,11 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
       if (nd == 1) continue;  // both faces see identical states: zero divergence
       const int M = d == 0 ? L::M0 : (d == 1 ? L::M1 : L::M2);
       const int Rd = d == 0 ? L::R0 : (d == 1 ? L::R1 : L::R2);
-      RT* const remd = rem + NC * (d == 0 ? 0 : (d == 1 ? L::R0 : L::R0 + L::R1));
+      RT* const remd = rem + NE * (d == 0 ? 0 : (d == 1 ? L::R0 : L::R0 + L::R1));
       for (int f = tid; f < M; f += kBlock)
         cfl = fmax(cfl, eval_face<RT, TX, TY, TZ, DO_T, DO_PI, PI_SRC, BK>(e, u, pi, p, eos, tauf,
-                                                                             q, d, f, lds + f, M));
+                                                                             q, d, f, lds + f, M,
+                                                                             ez));
       __syncthreads();
       if (q.active) {
         int fm, fp;
@@ -958,7 +962,8 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
         const RT rinv = (RT)(d == 0 ? p.inv_dx : (d == 1 ? p.inv_dy : p.inv_de / tauf));
   #pragma unroll
         for (int k = 0; k < NC; ++k)  // only the components this pass evaluates
-          if (k < 4 ? DO_T : DO_PI) R[k] -= (double)((ap[k * sp] - am[k * sm]) * rinv);
+          if (k < 4 ? DO_T : DO_PI)
+            R[k] -= (double)((ap[(k - K0) * sp] - am[(k - K0) * sm]) * rinv);
       }
       __syncthreads();
     }
@@ -1000,7 +1005,7 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
         } else {
   #pragma unroll
           for (int k = 0; k < NC; ++k)
-            if (k < 4 ? DO_T : DO_PI) lds[k * F + f] = RT(0);
+            if (k < 4 ? DO_T : DO_PI) lds[(k - K0) * F + f] = RT(0);
         }
       }
       __syncthreads();
@@ -1019,7 +1024,8 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
         const RT rinv = (RT)inv_del;
   #pragma unroll
         for (int k = 0; k < NC; ++k)  // only the components this pass evaluates
-          if (k < 4 ? DO_T : DO_PI) R[k] -= (double)((lds[k * F + fp] - lds[k * F + fm]) * rinv);
+          if (k < 4 ? DO_T : DO_PI)
+            R[k] -= (double)((lds[(k - K0) * F + fp] - lds[(k - K0) * F + fm]) * rinv);
       }
       __syncthreads();
     }
@@ -1048,7 +1054,7 @@ constexpr int lds_doubles_allf() {
 // a net gain when these passes needed more registers (stage2_pi 10-16%,
 // stage2_T 1-5% on the 201x201x105 grids, with a few spilled registers; the
 // lambda_1 variant 8% in FP64 with 60 bytes of spill, 13% in FP32); the plain
-// stage2_pi now fits 123 VGPRs (FP64, four waves) and 91 (FP32, five) without
+// stage2_pi now fits 126 VGPRs (FP64, four waves) and 92 (FP32, five) without
 // it.  Stage1 loses from the cap, so it has none, nor has the bulk variant of
 // stage2_pi (it spilled 96 bytes a lane under the cap: 1.06 ms against 0.75 ms
 // without it; its stage2_T keeps the cap).  NOCAP = true asks for no bound.
@@ -1445,7 +1451,7 @@ __device__ __forceinline__ void first_estimate_cell(const DFields& f, const Step
 template <typename RT, int TX, int TY, int TZ>
 __global__ __launch_bounds__(kBlock) void k_first_estimate(const EventDesc* __restrict__ evs,
                                                             GroupTable gt) {
-  __shared__ RT lds[lds_doubles<TX, TY, TZ>()];
+  __shared__ RT lds[lds_doubles<TX, TY, TZ, 4>()];
   const Ctx cx = load_ctx(evs, gt, 0);
   const DFields& f = cx.f;
   const StepParams& p = cx.p;
@@ -1639,7 +1645,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     BK || (NET && !L1) ? 3 : (NET ? 2 : (sizeof(RT) == 4 ? 5 : 1))))) void k_stage1(const EventDesc* __restrict__ evs,
                                                     GroupTable gt) {
   constexpr int NQ = BK ? 12 : 10;
-  __shared__ RT lds[lds_doubles<TX, TY, TZ, 4 + NQ, true>()];
+  __shared__ RT lds[lds_doubles<TX, TY, TZ, VISC ? 4 + NQ : 4, true>()];
   __shared__ GeoWaves shgeo;
   const Ctx cx = load_ctx(evs, gt, 0);
   const DFields& f = cx.f;
@@ -1780,15 +1786,17 @@ __device__ __forceinline__ bool stage2_pi_cell(const DFields& f, const StepParam
 
 // Stage 2, part 1 (tau_{n+1}): pi^{n+1} = [ (u^n pi^n + u* pi')/2 + h/2 R_pi(e', u', pi') ] / u'^tau.
 // BK: Pi^{n+1} and n^{n+1} the same way.  The relaxation source comes before the
-// face rounds: 123 VGPRs in FP64 (four waves per SIMD; 139 and three with the
+// face rounds: 126 VGPRs in FP64 (four waves per SIMD; 139 and three with the
 // source after them: 0.45 -> 0.40 ms on the 201x201x105 hotspot grid, 1.04 ->
-// 0.96 ms without vacuum), 91 in FP32 (five waves: 0.32 -> 0.30 ms).
+// 0.96 ms without vacuum), 92 in FP32 (five waves: 0.32 -> 0.30 ms).  Only pi~'s 10
+// components are in LDS (32 KB in FP64 with the faces split as in FaceLayout), which
+// leaves room for four workgroups per CU.
 template <typename RT, int TX, int TY, int TZ, bool L1, bool BK = false>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(pi_waves<RT, TX, TY, TZ, BK, BK ? 16 : 14>()))) void k_stage2_pi(
     const EventDesc* __restrict__ evs, GroupTable gt) {
   constexpr int NQ = BK ? 12 : 10;
-  __shared__ RT lds[lds_doubles<TX, TY, TZ, 4 + NQ>()];
+  __shared__ RT lds[lds_doubles<TX, TY, TZ, NQ, true>()];
   const Ctx cx = load_ctx(evs, gt, 1);
   const DFields& f = cx.f;
   const StepParams& p = cx.p;
@@ -1817,7 +1825,7 @@ __attribute__((amdgpu_waves_per_eu(pi_waves<RT, TX, TY, TZ, BK, BK ? 16 : 14>())
   // the source first, as in stage 1
   stage2_pi_source<RT, L1, BK>(f, p, eos, g, q, R);
   // pi~' was regulated with e^n in stage 1: zero wherever e^n is (vac_zero)
-  tile_divergence<RT, TX, TY, TZ, false, true, 2, BK, false, false, false>(
+  tile_divergence<RT, TX, TY, TZ, false, true, 2, BK, true, false, false>(
       f.e1, f.u1, f.pi1, p, eos, tf, q, R, lds, f.e, box);
   const bool quiet = stage2_pi_cell<RT, BK>(f, p, eos, q, R);
   if (p.quiet_r[0] > 0) {
@@ -2026,7 +2034,7 @@ template <typename RT, int TX, int TY, int TZ, bool DO_T, bool DO_PI, bool BK>
 __device__ __forceinline__ void small_divergence(const RT* lds, const StepParams& p, double tauf,
                                                  const Pos& q, double* R) {
   using L = SmallLayout<TX, TY, TZ>;
-  constexpr int NC = BK ? 16 : 14;
+  constexpr int NC = BK ? 16 : 14, K0 = DO_T ? 0 : 4;
   if (!q.active) return;
 #pragma unroll
   for (int d = 0; d < L::AXES; ++d) {
@@ -2047,7 +2055,7 @@ __device__ __forceinline__ void small_divergence(const RT* lds, const StepParams
 #pragma unroll
     for (int k = 0; k < NC; ++k)
       if (k < 4 ? DO_T : DO_PI)
-        R[k] -= (double)((lds[k * L::FT + fp] - lds[k * L::FT + fm]) * rinv);
+        R[k] -= (double)((lds[(k - K0) * L::FT + fp] - lds[(k - K0) * L::FT + fm]) * rinv);
   }
 }
 
@@ -2149,7 +2157,7 @@ template <typename RT, int TX, int TY, int TZ, bool L1, bool BK = false>
 __global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_stage2_pi_small(
     const EventDesc* __restrict__ evs, GroupTable gt) {
   constexpr int NQ = BK ? 12 : 10;
-  __shared__ RT lds[(4 + NQ) * SmallLayout<TX, TY, TZ>::FT];
+  __shared__ RT lds[NQ * SmallLayout<TX, TY, TZ>::FT];
   KTMI_SMALL_PROLOGUE(1);
   if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) return;
   double R[4 + NQ];

@@ -39,45 +39,31 @@ namespace {
 constexpr int kSurfBlock = 256;
 
 // Hot fraction of a tetrahedron on which phi is linear (vertex values v0..v3).
-// The hot and cold vertices are taken in vertex order; every branch is a sum or
-// product of positive terms.
+// The hot and cold vertices are taken in vertex order; every term is a sum or
+// product of positive ones.  Without branches, since the lanes of a wave hold every
+// case: with one vertex apart from the three others (value s0; r0, r1, r2) its corner
+// is s0^3 / prod (s0 + r), hot or cold; with two hot (a, b) and two cold (c, d) the
+// volume is [a^2 b^2 + a b (a + b)(c + d) + c d (a^2 + a b + b^2)] / [(a+c)(a+d)(b+c)(b+d)],
+// whose quotient takes the place of the first one: 3 divisions instead of 7.
 __device__ __forceinline__ double tet_hot(double v0, double v1, double v2, double v3) {
-  const double v[4] = {v0, v1, v2, v3};
-  double p0 = 0.0, p1 = 0.0, p2 = 0.0, n0 = 0.0, n1 = 0.0, n2 = 0.0;
-  int np = 0, nn = 0;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const bool hot = v[t] > 0.0;
-    const double x = hot ? v[t] : -v[t];
-    if (hot) {
-      p0 = np == 0 ? x : p0;
-      p1 = np == 1 ? x : p1;
-      p2 = np == 2 ? x : p2;
-      ++np;
-    } else {
-      n0 = nn == 0 ? x : n0;
-      n1 = nn == 1 ? x : n1;
-      n2 = nn == 2 ? x : n2;
-      ++nn;
-    }
-  }
-  if (np == 0) return 0.0;
-  if (np == 4) return 1.0;
-  if (np == 1) {
-    const double a = p0;
-    return (a / (a + n0)) * (a / (a + n1)) * (a / (a + n2));
-  }
-  if (np == 3) {
-    const double c = n0;
-    if (c == 0.0) return 1.0;
-    return 1.0 - (c / (p0 + c)) * (c / (p1 + c)) * (c / (p2 + c));
-  }
-  // two hot (a, b) and two cold (c, d, magnitudes): the volume of {phi > 0} is
-  // [a^2 b^2 + a b (a + b)(c + d) + c d (a^2 + a b + b^2)] / [(a+c)(a+d)(b+c)(b+d)]
-  const double a = p0, b = p1, c = n0, d = n1;
-  const double num = a * a * b * b + a * b * (a + b) * (c + d) + c * d * (a * a + a * b + b * b);
-  const double den = (a + c) * (a + d) * (b + c) * (b + d);
-  return num / den;
+  const bool h0 = v0 > 0.0, h1 = v1 > 0.0, h2 = v2 > 0.0, h3 = v3 > 0.0;
+  const int np = (int)h0 + (int)h1 + (int)h2 + (int)h3;
+  const bool three = np == 3, two = np == 2;
+  // the set vertices: the hot ones, or the cold one of three hot
+  const bool b0 = h0 != three, b1 = h1 != three, b2 = h2 != three, b3 = h3 != three;
+  const double x0 = fabs(v0), x1 = fabs(v1), x2 = fabs(v2), x3 = fabs(v3);
+  const double s0 = b0 ? x0 : (b1 ? x1 : (b2 ? x2 : x3));  // first set
+  const double s1 = b3 ? x3 : (b2 ? x2 : x1);              // last set
+  const double r0 = !b0 ? x0 : (!b1 ? x1 : x2);            // first not set
+  const double rl = !b3 ? x3 : (!b2 ? x2 : x1);            // last not set
+  const double r1 = two ? rl : (b0 || b1 ? x2 : x1);       // second not set
+  const double num = s0 * s0 * s1 * s1 + s0 * s1 * (s0 + s1) * (r0 + r1) +
+                     r0 * r1 * (s0 * s0 + s0 * s1 + s1 * s1);
+  const double den = (s0 + r0) * (s0 + r1) * (s1 + r0) * (s1 + r1);
+  const double q = (two ? num : s0) / (two ? den : s0 + r0);
+  const double c = q * (s0 / (s0 + r1)) * (s0 / (s0 + rl));
+  const double f = two ? q : (three ? 1.0 - c : c);
+  return np == 0 ? 0.0 : (np == 4 ? 1.0 : f);
 }
 
 // Hot fraction of a 3-cube with corner values w[4 b0 + 2 b1 + b2]: mean over the
@@ -138,20 +124,6 @@ __host__ __device__ __forceinline__ long cube_count(long nx, long ny, long ne) {
   return (nx > 1 ? nx - 1 : 1) * (ny > 1 ? ny - 1 : 1) * (ne > 1 ? ne - 1 : 1);
 }
 
-// Whether hypercube id's 16 corners straddle e_f (some > e_f, some not).
-__device__ __forceinline__ bool straddles(const SurfaceArgs& a, int id) {
-  const gdouble* A = (const gdouble*)a.A;
-  const gdouble* B = (const gdouble*)a.B;
-  const Cube q = cube_of(a, id);
-  int nhot = 0;
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const gdouble* S = (c & 8) ? B : A;
-    nhot += (S[q.cell[c & 7]] - a.eps_f) > 0.0;
-  }
-  return nhot != 0 && nhot != 16;
-}
-
 // Every count / compaction workgroup covers kSpan consecutive hypercubes: kIt
 // rounds of kSurfBlock threads.  Scratch layout (words): [0, nblk) counts per
 // workgroup, then exclusive offsets in place; [nblk, nblk + kIt kWaves nblk) the
@@ -169,20 +141,85 @@ __device__ __forceinline__ long xcd_span(long b, long G) {
   return k * per + (k < rem ? k : rem) + b / 8;
 }
 
-// Pass 1: straddle masks and straddling hypercubes per workgroup.
-__global__ __launch_bounds__(kSurfBlock) void k_surface_count(SurfaceArgs a, int nblk) {
-  __shared__ int wc[kWaves];
+// Pass 1: straddle masks (some of the 16 corners > e_f, some not) and straddling
+// hypercubes per workgroup.  The lower corners of a span's hypercubes lie in one run of
+// cells (the next row's and the next eta included), the upper ones in another: the
+// workgroup reads both runs of both slices once, in order, keeps a bit per cell (e > e_f)
+// in LDS, and takes the 16 corners from there.  Bound by reading e, 2.1 times, against 8
+// loads per hypercube through the caches and a wait for each of 16 rounds of them before
+// (201x201x105: 37 -> 24 us).
+// Runs too long for the LDS (ne of thousands) are read corner by corner.
+constexpr int kCountBlock = 1024;
+constexpr int kRunWords = 288;  // 64-cell words of a run
+
+__global__ __launch_bounds__(kCountBlock) void k_surface_count(SurfaceArgs a, int nblk) {
+  constexpr int W = kCountBlock / 64;
+  __shared__ int wc[W];
+  __shared__ unsigned long long run[4][kRunWords + 1];
   const long ncube = cube_count(a.nx, a.ny, a.ne);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const gdouble* A = (const gdouble*)a.A;
+  const gdouble* B = (const gdouble*)a.B;
   gullong* blk = (gullong*)a.blocks;
   const long sb = xcd_span(blockIdx.x, nblk);
   gullong* masks = blk + nblk + sb * kIt * kWaves;
+  const unsigned cy = a.ny > 1 ? a.ny - 1 : 1, cz = a.ne > 1 ? a.ne - 1 : 1;
+  const int sx = a.nx > 1 ? a.ny * a.ne : 0, sy = a.ny > 1 ? a.ne : 0, sz = a.ne > 1;
+  auto first_corner = [&](long id) {
+    const unsigned u = (unsigned)(id < ncube ? id : ncube - 1);
+    const unsigned r = u / cz, k = u - r * cz, i = r / cy;
+    return (int)((r + i * (a.ny - cy)) * a.ne + k);  // (i ny + j) ne + k
+  };
+  const int c0 = first_corner(sb * kSpan);
+  const int len = first_corner(sb * kSpan + kSpan - 1) - c0 + sy + sz + 1;
+  const bool fits = len <= 64 * kRunWords;
+  if (fits) {
+    const gdouble* S[4] = {A + c0, A + c0 + sx, B + c0, B + c0 + sx};
+    for (int t = threadIdx.x; t - lane < len; t += 2 * kCountBlock) {
+      double v[2][4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = t + h * kCountBlock;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[h][q] = c < len ? S[q][c] : a.eps_f;
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int w = (t - lane + h * kCountBlock) >> 6;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const unsigned long long m = __ballot(v[h][q] > a.eps_f);
+          if (lane == 0 && w < kRunWords) run[q][w] = m;
+        }
+      }
+    }
+    __syncthreads();
+  }
   int nw = 0;
-  for (int it = 0; it < kIt; ++it) {
-    const long id = sb * kSpan + (long)it * kSurfBlock + threadIdx.x;
-    const bool cross = id < ncube && straddles(a, (int)id);
-    const unsigned long long mask = __ballot(cross);
-    if (lane == 0) masks[it * kWaves + wave] = mask;
+  for (int it = 0; it < kSpan / kCountBlock; ++it) {
+    const long id = sb * kSpan + (long)it * kCountBlock + threadIdx.x;
+    const int c = first_corner(id);
+    unsigned any = 0, all = 3;  // of the corners on the lower and the upper eta
+    auto corners = [&](unsigned two) {
+      any |= two;
+      all &= two;
+    };
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        if (fits) {
+          const int b = c - c0 + (r ? sy : 0);
+          const unsigned* w = (const unsigned*)run[q] + (b >> 5);
+          const unsigned two = __builtin_amdgcn_alignbit(w[1], w[0], b & 31);
+          corners(sz ? two & 3 : 3 * (two & 1));
+        } else {
+          const gdouble* e = (q & 2 ? B : A) + (q & 1 ? sx : 0) + (r ? sy : 0) + c;
+          corners((e[0] > a.eps_f ? 1u : 0u) | (e[sz] > a.eps_f ? 2u : 0u));
+        }
+      }
+    const unsigned long long mask = __ballot(id < ncube && any != 0 && all != 3);
+    if (lane == 0) masks[it * W + wave] = mask;
     nw += __popcll(mask);
   }
   if (lane == 0) wc[wave] = nw;
@@ -190,7 +227,7 @@ __global__ __launch_bounds__(kSurfBlock) void k_surface_count(SurfaceArgs a, int
   if (threadIdx.x == 0) {
     int n = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) n += wc[w];
+    for (int w = 0; w < W; ++w) n += wc[w];
     blk[sb] = (unsigned long long)n;
   }
 }
@@ -267,15 +304,19 @@ __global__ __launch_bounds__(kSurfBlock) void k_surface_compact(SurfaceArgs a, i
 // Pass 4: the element of every claimed slot below min(count, capacity).  Eight
 // lanes share one element: the 16 corner values go through LDS, lane t
 // evaluates the hot fraction of the 3-face normal to axis t/2 on side t%2 (its
-// six tetrahedra) and the even lane of each pair forms S_mu; every lane forms the
-// centre and the corner weights (the same arithmetic in each); lane t
-// interpolates fields t and t + 8.  Grid-stride over groups of elements; the
-// loop bound is block-uniform, so every thread reaches each barrier.
+// six tetrahedra) and the even lane of each pair forms S_mu; lane t divides out 4 of
+// the 32 edges' sign changes and sums the centre along axis t % 4; every lane forms
+// the corner weights (the same arithmetic in each); lane t interpolates fields t and
+// t + 8.  Grid-stride over groups of elements; the
+// loop bound is block-uniform, so every thread reaches each barrier.  Bound by its
+// arithmetic (20 us of 33 for the 201x201x105 event's surface; 44 with the divisions of
+// every tetrahedron's case and every edge in each lane), then by the corners' fields; 166
+// VGPRs, three waves per SIMD (four or five spill: 42 and 67 us).
 constexpr int kGroup = 8;
 constexpr int kElemPerBlock = kSurfBlock / kGroup;
 
-__global__ __launch_bounds__(kSurfBlock) void k_surface_elem(SurfaceArgs a) {
-  __shared__ double sphi[kElemPerBlock][16];
+__global__ __launch_bounds__(kSurfBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_surface_elem(SurfaceArgs a) {
+  __shared__ double sphi[kElemPerBlock][17], sedge[kElemPerBlock][4][17];  // (17: banks)
   const gdouble* A = (const gdouble*)a.A;
   const gdouble* B = (const gdouble*)a.B;
   gdouble* outp = (gdouble*)a.out;
@@ -300,11 +341,13 @@ __global__ __launch_bounds__(kSurfBlock) void k_surface_elem(SurfaceArgs a) {
     gdouble* r = outp + (act ? slot : 0) * kSurfRec;
     const int id = act ? (int)r[0] : 0;
     const Cube q = cube_of(a, id);
+    double v2[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int c = 2 * t + u;
       const gdouble* S = (c & 8) ? B : A;
-      sphi[g][c] = S[q.cell[c & 7]] - a.eps_f;
+      v2[u] = S[q.cell[c & 7]] - a.eps_f;
+      sphi[g][c] = v2[u];
     }
     __syncthreads();
     double w[8];
@@ -312,29 +355,41 @@ __global__ __launch_bounds__(kSurfBlock) void k_surface_elem(SurfaceArgs a) {
     for (int b = 0; b < 8; ++b) w[b] = sphi[g][face_corner(mu, side, b)];
     const double f = cube_hot(w);
     const double f_other = __shfl_xor(f, 1);
-    double phi[16];
+    // the sign change along each edge (corner c, axis): lane t those of axis t % 4 from the
+    // corners 4 (t / 4) ... of the 8 without that axis' bit
+    const int ax0 = t & 3, low = (8 >> ax0) - 1;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) phi[c] = sphi[g][c];
-    double cen[4] = {0.0, 0.0, 0.0, 0.0};
-    int ncross = 0;
+    for (int n4 = 0; n4 < 4; ++n4) {
+      const int b = 4 * (t >> 2) + n4, c = ((b & ~low) << 1) | (b & low);
+      const double p1 = sphi[g][c], p2 = sphi[g][c | (low + 1)];
+      sedge[g][ax0][c] = p1 / (p1 - p2);
+    }
+    // hot corners of the element (bit c), and per axis the edges that cross
+    const int sh = (int)(threadIdx.x & 63 & ~(kGroup - 1));
+    auto spread = [](unsigned x) {  // bit i -> bit 2 i
+      x = (x | x << 4) & 0x0f0fu;
+      x = (x | x << 2) & 0x3333u;
+      return (x | x << 1) & 0x5555u;
+    };
+    const unsigned hot = spread((unsigned)(__ballot(v2[0] > 0.0) >> sh) & 0xffu) |
+                         spread((unsigned)(__ballot(v2[1] > 0.0) >> sh) & 0xffu) << 1;
+    const unsigned cr[4] = {(hot ^ hot >> 8) & 0x00ffu, (hot ^ hot >> 4) & 0x0f0fu,
+                            (hot ^ hot >> 2) & 0x3333u, (hot ^ hot >> 1) & 0x5555u};
+    const int ncross = __popc(cr[0]) + __popc(cr[1]) + __popc(cr[2]) + __popc(cr[3]);
+    __syncthreads();
+    // the centre along axis t % 4: the edges in order of corner, then axis
+    double cm = 0.0;
 #pragma unroll
-    for (int c = 0; c < 16; ++c)
+    for (int c = 0; c < 16; ++c) {
+      const double s = sedge[g][ax0][c], bit = (double)((c >> (3 - ax0)) & 1);
 #pragma unroll
-      for (int ax = 0; ax < 4; ++ax) {
-        const int bitm = 1 << (3 - ax);
-        if (c & bitm) continue;
-        const int c2 = c | bitm;
-        if ((phi[c] > 0.0) == (phi[c2] > 0.0)) continue;
-        const double s = phi[c] / (phi[c] - phi[c2]);
+      for (int ax = 0; ax < 4; ++ax)
+        if (!(c & (8 >> ax))) cm += (cr[ax] >> c) & 1 ? (ax == ax0 ? s : bit) : 0.0;
+    }
+    cm /= (double)ncross;
+    double cen[4];
 #pragma unroll
-        for (int a2 = 0; a2 < 4; ++a2) {
-          const int bb = (c >> (3 - a2)) & 1;
-          cen[a2] += (a2 == ax) ? s : (double)bb;
-        }
-        ++ncross;
-      }
-#pragma unroll
-    for (int a2 = 0; a2 < 4; ++a2) cen[a2] /= (double)ncross;
+    for (int a2 = 0; a2 < 4; ++a2) cen[a2] = __shfl(cm, sh + a2);
     const double tc = a.tauA + cen[0] * ext[0];
     if (act) {
       if (side == 0) {  // S_mu = V_mu (f_lo - f_hi), V_mu over the other axes in order
@@ -362,7 +417,7 @@ __global__ __launch_bounds__(kSurfBlock) void k_surface_elem(SurfaceArgs a) {
         }
         wgt[c] = wv;
       }
-#pragma unroll
+#pragma unroll 1  // (both at once spill)
       for (int h2 = 0; h2 < 2; ++h2) {
         const int fld = t + kGroup * h2;
         if (fld >= 14) continue;
@@ -392,7 +447,7 @@ size_t surface_scratch_words(long nx, long ny, long ne) {
 
 int launch_surface(const SurfaceArgs& a, hipStream_t s) {
   const long nblk = (cube_count(a.nx, a.ny, a.ne) + kSpan - 1) / kSpan;
-  hipLaunchKernelGGL(k_surface_count, dim3((unsigned)nblk), dim3(kSurfBlock), 0, s, a, (int)nblk);
+  hipLaunchKernelGGL(k_surface_count, dim3((unsigned)nblk), dim3(kCountBlock), 0, s, a, (int)nblk);
   hipLaunchKernelGGL(k_surface_offsets, dim3(1), dim3(1024), 0, s, a, (int)nblk);
   if (a.capacity > 0) {
     hipLaunchKernelGGL(k_surface_compact, dim3((unsigned)nblk), dim3(kSurfBlock), 0, s, a,

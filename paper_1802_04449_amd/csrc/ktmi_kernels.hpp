@@ -334,17 +334,23 @@ __device__ __forceinline__ int lane_of(int x, int l) { return __builtin_amdgcn_r
 // vacuum takes a short path that gives the same bits and stores only what is not there yet;
 // one marked as matter skips the test.  Cleared flags say nothing: the fields are tested.
 // us a pass (stage 1 / 2pi / 2T): 201x201x105 hotspots, 82% vacuum, 410/376/327 ->
-// 350/298/270, mixed 320/284/279 -> 293/228/225; 385x385x129 2254/2057/1658 ->
-// 1952/1626/1411; 101x99x65 without vacuum 170/150/114 -> 167/150/115.
+// 350/298/263, mixed 320/284/279 -> 292/228/220; 385x385x129 2254/2057/1658 ->
+// 1948/1626/1383; 101x99x65 without vacuum 170/150/114 -> 167/150/114.  What is left of a
+// vacuum tile is its workgroup's start and end: 18200 of them take 40 us even in stage 2pi,
+// which reads nothing else (T~ loaded ahead of the marks: no gain, mixed stage 1 292 -> 328).
 enum : int { kMarkNone = 0, kMarkVac = 1, kMarkVac2 = 2, kMarkMatter = 3 };
 __device__ __forceinline__ int mark_of(int flags) { return (flags >> 1) & 3; }
-// kPiZeros (stage 2pi's flag): pi~ of the whole tile is stored as zero.
+// kPiZeros (stage 2pi's flag): the box is vacuum in e^n and e', and pi~ of the whole tile
+// stored as zero.
 constexpr int kPiZeros = 2;
 
 // What the marks say of the box that the tile's face stencils read, wave-uniform; a second
 // field's marks (n2) have to agree.  Tiles too short for 64 lanes to hold their neighbours'
 // marks are never kBoxClear.
 enum : int { kBoxUnknown = 0, kBoxOwnVac, kBoxMatter, kBoxClear };
+__device__ __forceinline__ int box_of_own(int mark) {
+  return mark == kMarkMatter ? kBoxMatter : (mark != kMarkNone ? kBoxOwnVac : kBoxUnknown);
+}
 template <int TX, int TY, int TZ, bool TWO>
 __device__ __forceinline__ int box_marks(const TileGrid& tg, const gint* n1, const gint* n2,
                                          int tile) {
@@ -370,8 +376,7 @@ __device__ __forceinline__ int box_marks(const TileGrid& tg, const gint* n1, con
   const bool vac = (m1 == kMarkVac || m1 == kMarkVac2) && (m2 == kMarkVac || m2 == kMarkVac2);
   if (FIT && __ballot(!vac) == 0) return kBoxClear;
   const int o1 = lane_of(m1, OWN), o2 = lane_of(m2, OWN);
-  if (o1 == kMarkMatter || (TWO && o2 == kMarkMatter)) return kBoxMatter;
-  return o1 != kMarkNone ? kBoxOwnVac : kBoxUnknown;
+  return TWO && o2 == kMarkMatter ? kBoxMatter : box_of_own(o1);
 }
 
 // Max over the tile's faces of c / Delta when every face is a vacuum face.
@@ -1962,8 +1967,12 @@ __attribute__((amdgpu_waves_per_eu(s2t_waves<RT, TX, TY, TZ, BK>()))) void k_sta
     if (threadIdx.x == 0) cx.qnext[cx.tile] = own | 1;
     return;
   }
-  const int box = box_marks<TX, TY, TZ, false>(cx.tg, cx.t1same, nullptr, cx.tile);
-  const bool t1s = (cx.t1same[cx.tile] & 1) != 0;
+  // viscous: stage 2pi has found the vacuum boxes
+  const int now1 = cx.t1same[cx.tile];
+  const int box = !VISC ? box_marks<TX, TY, TZ, false>(cx.tg, cx.t1same, nullptr, cx.tile)
+                  : lane_of(cx.qpi[cx.tile], 0) & kPiZeros ? kBoxClear
+                                                           : box_of_own(mark_of(lane_of(now1, 0)));
+  const bool t1s = (now1 & 1) != 0;
   const int mark = mark_of(own);  // of e^n
   bool matter, quiet;
   if (box == kBoxClear && p.vac_zero) {

@@ -219,7 +219,9 @@ int ktmi_tile_count(void);
 int ktmi_tile_shape(int t, int *tx, int *ty, int *tz);
 
 /* Selects the tile shape used by later launches (-1 = automatic: fewest padded
- * thread slots).  The workspace is sized for every shape. */
+ * thread slots; a small FP64 event without the network then runs on kernels of
+ * its own, with the same fields and counters).  The workspace is sized for every
+ * shape. */
 int ktmi_set_tile(ktmi_handle *h, int t);
 int ktmi_get_tile(const ktmi_handle *h);
 

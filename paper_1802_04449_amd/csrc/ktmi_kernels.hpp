@@ -833,7 +833,8 @@ __device__ __forceinline__ double tile_divergence(const GField& e,
   if ((PI_SRC == 2 || KTMI_S1_TILE_TEST) && box != kBoxMatter) {
     constexpr int BX = TX + 4, BY = TY + 4, BZ = TZ + 4, NB = BX * BY * BZ;
     // the tile's own cells first (one load per thread, which the cell phase
-    // reuses): a tile with matter skips the rest of the test
+    // reuses): a tile with matter skips the rest of the test, a tile marked as such (box)
+    // all of it, a tile marked as vacuum this first part
     int nz = 0, any = 0;
     if (box != kBoxOwnVac) {
       nz = q.active && e[q.c] != 0.0;
@@ -1068,11 +1069,11 @@ constexpr int pi_waves() {
   return !NOCAP && 163840 / (int)(lds_doubles<TX, TY, TZ, NC>() * sizeof(RT) + 512) >= 3 ? 3 : 1;
 }
 
-// Waves per SIMD asked of stage 2T: four without bulk in FP64 (its streamed faces
-// need 143 VGPRs; under the four-wave cap of 128 a few spill, and the pass still
-// runs faster: 0.46 -> 0.42 ms on the 201x201x105 hotspot grid, 0.86 -> 0.84 ms
-// on the grid without vacuum), five in FP32 (95 VGPRs, no spill: 0.36 -> 0.33 ms
-// and 0.64 -> 0.60 ms); with bulk as the other stage-2 passes.
+// Waves per SIMD asked of stage 2T: four without bulk in FP64 (127 VGPRs with 2 spilled;
+// three or five waves are slower, and when its faces needed 143 VGPRs the cap took it
+// from 0.46 to 0.42 ms on the 201x201x105 hotspot grid, 0.86 to 0.84 ms without vacuum),
+// five in FP32 (90 VGPRs, no spill: 0.36 -> 0.33 ms and 0.64 -> 0.60 ms); with bulk as the
+// other stage-2 passes.
 template <typename RT, int TX, int TY, int TZ, bool BK>
 constexpr int s2t_waves() {
   return !BK ? (sizeof(RT) == 4 ? 5 : 4) : pi_waves<RT, TX, TY, TZ, false>();
@@ -1637,11 +1638,11 @@ __device__ __forceinline__ void stage1_cell_clear(const DFields& f, const StepPa
 // Stage 1 at tau_n (predictor) for the ideal (VISC = false) or viscous path;
 // BK (viscous only): also Pi and n, with P + Pi in T~ and in the root solve.
 // The cell's sources come before the face rounds, so the shear source's
-// gradients and the divergence accumulators are never live together: 137 VGPRs
+// gradients and the divergence accumulators are never live together: 147 VGPRs
 // in FP64 (three waves per SIMD, which its 45 KB of LDS also allows; 161 with the
 // sources after the rounds), 103 in FP32 (four waves; 134 before, and the pass
 // went from 0.54 to 0.49 ms on the 201x201x105 hotspot grid), which asks for
-// five (96 VGPRs with 14 spilled: 0.43 -> 0.41 ms there).  The bulk variant
+// five (96 VGPRs with 22 spilled: 0.43 -> 0.41 ms there).  The bulk variant
 // and the network variants ask for three waves (uncapped, the matrix-core
 // results take 32 accumulation registers on top; capped, they stay in VGPRs
 // without spills), the network variant with the lambda_1 term two (else one).

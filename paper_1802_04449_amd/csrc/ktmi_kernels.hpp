@@ -334,8 +334,8 @@ __device__ __forceinline__ int lane_of(int x, int l) { return __builtin_amdgcn_r
 // vacuum takes a short path that gives the same bits and stores only what is not there yet;
 // one marked as matter skips the test.  Cleared flags say nothing: the fields are tested.
 // us a pass (stage 1 / 2pi / 2T): 201x201x105 hotspots, 82% vacuum, 410/376/327 ->
-// 350/298/263, mixed 320/284/279 -> 292/228/220; 385x385x129 2254/2057/1658 ->
-// 1948/1626/1383; 101x99x65 without vacuum 170/150/114 -> 167/150/114.  What is left of a
+// 346/298/263, mixed 320/284/279 -> 278/228/220; 385x385x129 2254/2057/1658 ->
+// 1938/1626/1383; 101x99x65 without vacuum 170/150/114 -> 167/150/114.  What is left of a
 // vacuum tile is its workgroup's start and end: 18200 of them take 40 us even in stage 2pi,
 // which reads nothing else (T~ loaded ahead of the marks: no gain, mixed stage 1 292 -> 328).
 enum : int { kMarkNone = 0, kMarkVac = 1, kMarkVac2 = 2, kMarkMatter = 3 };
@@ -1612,23 +1612,17 @@ __device__ __forceinline__ bool stage1_solve(const DFields& f, const StepParams&
 }
 
 // Stage 1 of a cell whose tile's box is vacuum (kBoxClear): no flux and no source (P(0) = 0),
-// so T~' = T~^n up to the sign of a zero, and pi~' = 0 (stored only where stage 2pi would
-// read it, unless the step before left it there).
+// so T~' = T~^n (up to the sign of a zero, which T~^{n+1} and the root solve do not see: left
+// unstored without a test), and pi~' = 0 (stored only where stage 2pi would read it, unless
+// the step before left it there).
 template <typename RT, bool VISC, bool BK>
 __device__ __forceinline__ void stage1_cell_clear(const DFields& f, const StepParams& p,
-                                                  const Geo& g, const Pos& q, double* K, double* T1,
-                                                  bool& t1same, bool pi1_stored) {
+                                                  const Geo& g, const Pos& q, double* K,
+                                                  bool pi1_stored) {
   if (!q.active) return;
-#pragma unroll
-  for (int nu = 0; nu < 4; ++nu) {
-    const double t0 = f.T[nu][q.c];
-    // the geometric source of e = 0 is -0
-    T1[nu] = t0 + (!g.cart && (nu == 0 || nu == 3) ? -0.0 : 0.0);
-    t1same = t1same && __builtin_bit_cast(long long, T1[nu]) == __builtin_bit_cast(long long, t0);
-  }
   const double inv_tf1 = 1.0 / (g.cart ? 1.0 : g.tau1);
 #pragma unroll
-  for (int nu = 0; nu < 4; ++nu) K[nu] = T1[nu] * inv_tf1;
+  for (int nu = 0; nu < 4; ++nu) K[nu] = f.T[nu][q.c] * inv_tf1;
   if (VISC && (BK || !KTMI_PI1_SPARSE) && !pi1_stored) {
 #pragma unroll
     for (int m = 0; m < (BK ? 12 : 10); ++m) stq<RT>(f.pi1[m], q.c, 0.0);
@@ -1674,16 +1668,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
   if (clear) {
     const int own = cx.t1same[cx.tile];
     v.cfl = vacuum_cfl<RT>(p, tf) * p.h;
-    stage1_cell_clear<RT, VISC, BK>(f, p, g, q, K, T1, t1same,
-                                    mark_of(cx.qcur[cx.tile]) == kMarkVac2);
-    const int all_same = __syncthreads_and(t1same);
-    if (!all_same && q.active) {
-#pragma unroll
-      for (int nu = 0; nu < 4; ++nu) st_cell(f.T1[nu] + q.c, T1[nu]);
-    }
+    stage1_cell_clear<RT, VISC, BK>(f, p, g, q, K, mark_of(cx.qcur[cx.tile]) == kMarkVac2);
     const bool m = stage1_solve<RT, NET, BK>(f, p, eos, q, K, 0.0, 0.0, v, mark_of(own) == kMarkVac);
     const bool any = block_partials(v, f.partial, cx.tg.ntiles, cx.tile, nullptr, m);
-    const int now = (any ? kMarkMatter : kMarkVac) << 1 | (all_same ? 1 : 0);
+    const int now = (any ? kMarkMatter : kMarkVac) << 1 | 1;
     if (threadIdx.x == 0 && now != own) cx.t1same[cx.tile] = now;
     return;
   }

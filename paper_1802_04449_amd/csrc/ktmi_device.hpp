@@ -70,9 +70,12 @@ struct EosDev {
 // ---------------------------------------------------------------------------
 // FP64 reciprocals, quotients and square roots.  FAST (the FP64 passes): from the hardware
 // estimates (v_rcp_f64, v_rsq_f64: about 26 bits), refined with fused multiply-adds to
-// within an ulp.  The arguments here are normal numbers away from the ends of the FP64
-// range, so the scaling and special-case selects of the general sequences (11 and 17
-// instructions) are left out; a zero or infinite divisor gives NaN.  The mixed passes keep
+// within an ulp.  The general sequences (11 and 17 instructions) also scale operands near the
+// ends of the FP64 range, which the arguments here leave alone, and select the results of
+// zero and infinite ones, which give NaN here: in the Newton steps a NaN is a step outside
+// the bracket.  Where a state may overflow otherwise (the bracket, 1 / sqrt((E + P)(e + P)),
+// the regulator), quot<FAST, true> ends with the division's fix-up instruction and inv_root
+// selects its 0, as IEEE operations give.  The mixed passes keep
 // the general sequences: their FP32 fluxes amplify a last-bit difference of the FP64 state
 // to FP32 rounding, so that a run would become another sample of it.
 // ---------------------------------------------------------------------------
@@ -83,13 +86,14 @@ __device__ __forceinline__ double recip(double x) {
   const double e = __builtin_fma(-x, y, 1.0);
   return __builtin_fma(y, __builtin_fma(e, e, e), y);  // y (1 + e + e^2)
 }
-template <bool FAST>
+template <bool FAST, bool FIX = false>
 __device__ __forceinline__ double quot(double a, double b) {
   if constexpr (!FAST) return a / b;
   const double y = recip<true>(b), q = a * y;
-  return __builtin_fma(__builtin_fma(-b, q, a), y, q);  // residual correction
+  const double r = __builtin_fma(__builtin_fma(-b, q, a), y, q);  // residual correction
+  return FIX ? __builtin_amdgcn_div_fixup(r, b, a) : r;
 }
-// sqrt(x), x > 0: one Goldschmidt step on (x y, y / 2), then a residual correction.
+// sqrt(x), 0 < x < inf: one Goldschmidt step on (x y, y / 2), then a residual correction.
 template <bool FAST>
 __device__ __forceinline__ double root(double x) {
   if constexpr (!FAST) return sqrt(x);
@@ -100,13 +104,13 @@ __device__ __forceinline__ double root(double x) {
   h = __builtin_fma(h, r, h);
   return __builtin_fma(__builtin_fma(-g, g, x), h, g);
 }
-// 1 / sqrt(x), x > 0: y (1 + e/2 + 3 e^2/8), e = 1 - x y^2.
+// 1 / sqrt(x), x > 0: y (1 + e/2 + 3 e^2/8), e = 1 - x y^2; 0 for x = inf.
 template <bool FAST>
 __device__ __forceinline__ double inv_root(double x) {
   if constexpr (!FAST) return 1.0 / sqrt(x);
   const double y = __builtin_amdgcn_rsq(x);
   const double e = __builtin_fma(-(x * y), y, 1.0);
-  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+  return y == 0.0 ? 0.0 : __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
 // Whether the passes of precision RT take them, and sqrt in the passes' flux type.
 template <typename RT>
@@ -263,7 +267,7 @@ __device__ inline Prim con2prim(const EosDev& q, const StepParams& p, double E, 
     M2 = K1 * K1 + K2 * K2 + K3 * K3;
     flags |= kClamp;
   }
-  double lo = E - quot<FAST>(M2, B);
+  double lo = E - quot<FAST, true>(M2, B);
   lo = lo < 0.0 ? 0.0 : lo;
   double hi = E;
   const double lo0 = lo, hi0 = hi;

@@ -240,12 +240,14 @@ int ktmi_set_graph(ktmi_handle *h, int on);
  * values its buffers hold (zero fluxes, zero sources, T~ unchanged).  Fields
  * and diagnostics equal those of the full computation bit for bit.  Needs an
  * EoS with P(0) = 0 (KTMI_ESTATE otherwise, also when a later table breaks
- * it).  Turning it on or off, or changing the tile shape, marks every tile
+ * it).  Turning it on or off, changing the tile shape, or stepping alone after a
+ * group made with another one (and the other way round) marks every tile
  * as not quiet, so the next step computes all of them.  A group uses the
  * setting its members had when it was created. */
 int ktmi_set_quiet_skip(ktmi_handle *h, int on);
 
-/* Number of quiet tiles after the last step, and of tiles.  Synchronizes. */
+/* Number of quiet tiles after the last step, and of tiles of the shape it ran with.
+ * Synchronizes. */
 int ktmi_quiet_tiles(ktmi_handle *h, long *quiet, long *total);
 
 /* Groups: step many events (possibly of different grids and modes) together.

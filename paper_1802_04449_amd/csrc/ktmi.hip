@@ -222,6 +222,10 @@ struct ktmi_handle {
   bool mlp_ok = false;
   // quiet-tile skipping (off by default); P of the EoS at e = 0 (must be 0 for it)
   bool quiet_on = false;
+  // whose the per-tile flags in the workspace are (own_flags): tile index of the launches that
+  // left them (-1: cleared), and whether those skipped quiet tiles
+  int flags_tile = -1;
+  bool flags_quiet = false;
   double eos_p0 = 0.0;
   double p_at0 = 0.0;  // P as the device lookups give it at e = 0 (first row, or 0)
   int mlp_mode = KTMI_MLP_FP32;
@@ -330,7 +334,11 @@ static TileGrid tile_grid(const ktmi_desc* d, const TileShape& t) {
   g.ntiles = g.ntx * g.nty * g.ntz;
   return g;
 }
-static TileGrid tile_grid(const ktmi_desc* d, int t) { return tile_grid(d, kTiles[t]); }
+// Shape of a tile index of the launches: kTiles, then kSmallTiles.
+static const TileShape& tile_shape(int t) {
+  return t < kNumTiles ? kTiles[t] : kSmallTiles[t - kNumTiles];
+}
+static TileGrid tile_grid(const ktmi_desc* d, int t) { return tile_grid(d, tile_shape(t)); }
 
 // Default tile: fewest padded thread slots, counting double for shapes whose eta
 // extent is shorter than min(ne, 16) (their lanes stride across eta rows, so
@@ -444,8 +452,7 @@ static StepParams step_params(const ktmi_handle* h) {
   p.vac_zero = h->d.pi_reg > 0.0 && h->p_at0 == 0.0;
   // quiet tiles: neighbourhood radius in tiles covering 6 cells per axis
   TileGrid tg;
-  const int rt = run_tile(h, &tg);
-  const TileShape& ts = rt < kNumTiles ? kTiles[rt] : kSmallTiles[rt - kNumTiles];
+  const TileShape& ts = tile_shape(run_tile(h, &tg));
   const int td[3] = {ts.tx, ts.ty, ts.tz};
   for (int a = 0; a < 3; ++a) p.quiet_r[a] = h->quiet_on ? (6 + td[a] - 1) / td[a] : 0;
   p.guess = h->d.guess;
@@ -589,21 +596,36 @@ static int enqueue_step(ktmi_handle* h) {
 
 // Marks every tile as neither quiet nor known to be vacuum (the next step computes and tests
 // them all).
-static int clear_quiet(ktmi_handle* h) {
+static int clear_quiet(ktmi_handle* h, hipStream_t s) {
   if (!h->bound) return KTMI_OK;
   const int n = (int)quiet_doubles(&h->d);
-  hipLaunchKernelGGL(k_zero, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, h->stream,
+  hipLaunchKernelGGL(k_zero, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
                      (double*)h->f.quiet, n);
   HIP_TRY(h, hipGetLastError());
+  h->flags_tile = -1;
+  return KTMI_OK;
+}
+
+// Before launches with the given tile index: the flags are per tile of that shape, and the
+// small-event kernels write theirs only when quiet tiles are skipped.  Flags that launches of
+// another kind left (a group keeps the tile and the quiet setting its members had when it was
+// made, while they may be stepped alone with others) are cleared.
+static int own_flags(ktmi_handle* h, hipStream_t s, int tile, bool quiet) {
+  if (h->flags_tile == tile && h->flags_quiet == quiet) return KTMI_OK;
+  if (h->flags_tile != -1)
+    if (int rc = clear_quiet(h, s)) return rc;
+  h->flags_tile = tile;
+  h->flags_quiet = quiet;
   return KTMI_OK;
 }
 
 static int finish_initial(ktmi_handle* h) {
   if (int rc = upload_event(h)) return rc;
   hipLaunchKernelGGL(k_set_clock, dim3(1), dim3(64), 0, h->stream, h->clock, h->tau);
-  if (int rc = clear_quiet(h)) return rc;  // before the first estimate, which leaves marks
+  if (int rc = clear_quiet(h, h->stream)) return rc;  // before the first estimate, which leaves marks
   TileGrid tg;
   const int tile = run_tile(h, &tg);
+  if (int rc = own_flags(h, h->stream, tile, h->quiet_on)) return rc;
   int rc = launch(h, K_FIRST, [&] {
     launch_class(PASS_FIRST, h->stream, tile, h->d.precision, false, h->dev_ev, single_table(tg));
   });
@@ -935,6 +957,9 @@ int ktmi_step(ktmi_handle* h, int nsteps) {
   if (!h->ready) return fail(h, KTMI_ESTATE, "set an initial state first");
   if (nsteps < 0) return fail(h, KTMI_EINVAL, "negative step count");
   if (int rc = upload_event(h)) return rc;
+  TileGrid tg;
+  if (nsteps > 0)
+    if (int rc = own_flags(h, h->stream, run_tile(h, &tg), h->quiet_on)) return rc;
   const bool graph = h->use_graph && !h->timing;
   if (graph && !h->gexec) {  // capture one step; every step issues the same launches
     hipGraph_t g = nullptr;
@@ -998,12 +1023,9 @@ int ktmi_set_guess(ktmi_handle* h, int guess) {
     return fail(h, KTMI_EINVAL, "unknown guess mode");
   if (guess == KTMI_GUESS_MLP && !h->mlp_ok)
     return fail(h, KTMI_ESTATE, "guess mode KTMI_GUESS_MLP needs ktmi_set_mlp first");
-  TileGrid tg;
-  const int before = run_tile(h, &tg);
   h->d.guess = guess;
   h->ev_dirty = true;
-  // the network's instances keep the large-grid tiles: the flags are per tile
-  return run_tile(h, &tg) == before ? KTMI_OK : clear_quiet(h);
+  return KTMI_OK;
 }
 
 int ktmi_harvest(ktmi_handle* h, double* E, double* M, double* eps) {
@@ -1195,15 +1217,16 @@ int ktmi_set_tile(ktmi_handle* h, int t) {
   h->tile = h->tile_auto ? auto_tile(&h->d) : t;
   h->tg = tile_grid(&h->d, h->tile);
   h->ev_dirty = true;
-  return clear_quiet(h);  // flags are per tile of the old shape
+  return clear_quiet(h, h->stream);  // flags are per tile of the old shape
 }
 
 int ktmi_quiet_tiles(ktmi_handle* h, long* quiet, long* total) {
   if (!h || !quiet || !total) return KTMI_EINVAL;
   if (!h->ready) return fail(h, KTMI_ESTATE, "no state");
   TileGrid tg;
-  (void)run_tile(h, &tg);
-  const int nt = tg.ntiles;
+  int tile = run_tile(h, &tg);
+  if (h->flags_tile >= 0) tile = h->flags_tile;  // (a group's, if that stepped last)
+  const int nt = tile_grid(&h->d, tile).ntiles;
   std::vector<int> flags(nt);
   // the step with clock parity p writes flag buffer 1 - p: after an odd number
   // of steps the latest flags are in buffer 1
@@ -1223,7 +1246,7 @@ int ktmi_set_quiet_skip(ktmi_handle* h, int on) {
     return fail(h, KTMI_ESTATE, "quiet-tile skipping needs an EoS with P(0) = 0");
   h->quiet_on = on != 0;
   h->ev_dirty = true;
-  return clear_quiet(h);
+  return clear_quiet(h, h->stream);
 }
 
 size_t ktmi_group_workspace_bytes(int nev) {
@@ -1309,6 +1332,10 @@ int ktmi_group_create(ktmi_handle* const* hs, int nev, void* ws, size_t bytes, k
 int ktmi_group_step(ktmi_group* g, int nsteps) {
   if (!g) return KTMI_EINVAL;
   if (nsteps < 0) return group_fail(g, KTMI_EINVAL, "negative step count");
+  for (const auto& c : g->classes)
+    for (int m = c.first; nsteps > 0 && m < c.first + c.gt.nev; ++m)
+      if (int rc = own_flags(g->hs[m], g->stream, c.tile, g->host[m].p.quiet_r[0] > 0))
+        return group_fail(g, rc, g->hs[m]->err);
   if (g->use_graph && !g->gexec) {
     hipGraph_t gr = nullptr;
     hipError_t e = hipStreamBeginCapture(g->stream, hipStreamCaptureModeThreadLocal);

@@ -226,6 +226,7 @@ struct ktmi_handle {
   // left them (-1: cleared), and whether those skipped quiet tiles
   int flags_tile = -1;
   bool flags_quiet = false;
+  bool flags_stale = false;  // left with another EoS: cleared before the next step
   double eos_p0 = 0.0;
   double p_at0 = 0.0;  // P as the device lookups give it at e = 0 (first row, or 0)
   int mlp_mode = KTMI_MLP_FP32;
@@ -603,15 +604,18 @@ static int clear_quiet(ktmi_handle* h, hipStream_t s) {
                      (double*)h->f.quiet, n);
   HIP_TRY(h, hipGetLastError());
   h->flags_tile = -1;
+  h->flags_stale = false;
   return KTMI_OK;
 }
 
 // Before launches with the given tile index: the flags are per tile of that shape, and the
 // small-event kernels write theirs only when quiet tiles are skipped.  Flags that launches of
 // another kind left (a group keeps the tile and the quiet setting its members had when it was
-// made, while they may be stepped alone with others) are cleared.
+// made, while they may be stepped alone with others) are cleared, and those of steps with
+// another EoS (with P(0) != 0 the regulator leaves pi~ in the vacuum, which a mark of two
+// vacuum steps takes for zero once P(0) = 0).
 static int own_flags(ktmi_handle* h, hipStream_t s, int tile, bool quiet) {
-  if (h->flags_tile == tile && h->flags_quiet == quiet) return KTMI_OK;
+  if (h->flags_tile == tile && h->flags_quiet == quiet && !h->flags_stale) return KTMI_OK;
   if (h->flags_tile != -1)
     if (int rc = clear_quiet(h, s)) return rc;
   h->flags_tile = tile;
@@ -818,6 +822,7 @@ int ktmi_set_eos_conformal(ktmi_handle* h, double c_sb) {
   h->p_at0 = 0.0;
   h->eos_set = true;
   h->ev_dirty = true;
+  h->flags_stale = true;
   return KTMI_OK;
 }
 
@@ -871,6 +876,7 @@ int ktmi_set_eos_table(ktmi_handle* h, double e0, double de, int n, const double
   h->eos.cs2 = dC;
   h->eos_set = true;
   h->ev_dirty = true;
+  h->flags_stale = true;
   return KTMI_OK;
 }
 

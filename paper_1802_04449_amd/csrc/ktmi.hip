@@ -620,6 +620,7 @@ static int own_flags(ktmi_handle* h, hipStream_t s, int tile, bool quiet) {
     if (int rc = clear_quiet(h, s)) return rc;
   h->flags_tile = tile;
   h->flags_quiet = quiet;
+  h->flags_stale = false;
   return KTMI_OK;
 }
 

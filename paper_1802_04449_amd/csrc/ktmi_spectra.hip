@@ -61,12 +61,13 @@ struct SpecShape {
   int nby;    // workgroups over the transverse groups
 };
 
-// e^x = m 2^k with |m - 1| < 0.42 (finite x; |x| > 1e6 is cut there, where the value
-// over- or underflows all the same; NaN stays NaN): k = round(x log2 e), then the
-// Taylor series of e^r, |r| <= ln2 / 2, to r^13 / 13! (remainder < 1e-17).
+// e^x = m 2^k with |m - 1| < 0.42 (finite x; cut at |x| = 7e8, so that the sum of two such k
+// fits 32 bits: the two factors of a bin may cancel up to there, u~ of about 1e7; NaN stays
+// NaN): k = round(x log2 e), then the Taylor series of e^r, |r| <= ln2 / 2, to r^13 / 13!
+// (remainder < 1e-17).
 __device__ __forceinline__ double split_exp(double x, int& k) {
-  x = x > 1e6 ? 1e6 : x;
-  x = x < -1e6 ? -1e6 : x;
+  x = x > 7e8 ? 7e8 : x;
+  x = x < -7e8 ? -7e8 : x;
   const double kd = rint(x * 1.4426950408889634);
   double r = fma(kd, -0.6931471805599453, x);
   r = fma(kd, -2.3190468138462996e-17, r);

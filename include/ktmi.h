@@ -221,7 +221,7 @@ int ktmi_tile_shape(int t, int *tx, int *ty, int *tz);
 /* Selects the tile shape used by later launches (-1 = automatic: fewest padded
  * thread slots; a small FP64 event without the network then runs on kernels of
  * its own, with the same fields and counters).  The workspace is sized for every
- * shape. */
+ * shape.  ktmi_get_tile gives the shape, also of the automatic choice. */
 int ktmi_set_tile(ktmi_handle *h, int t);
 int ktmi_get_tile(const ktmi_handle *h);
 
@@ -253,8 +253,10 @@ int ktmi_quiet_tiles(ktmi_handle *h, long *quiet, long *total);
 /* Groups: step many events (possibly of different grids and modes) together.
  * Events are sorted into classes of equal (viscous, precision, tile); per class
  * and stage a single launch covers the tiles of all its events (at most 128 per
- * class), and one reduce launch serves them all.  The handles keep their own
- * workspaces and states; the group only needs a device table of
+ * class), and one reduce launch serves them all.  Small events with an automatic
+ * tile and more than one eta cell keep kernels of their own only while they do not
+ * fill the GPU together (diagnostics sums then round as with an explicit tile).  The
+ * handles keep their own workspaces and states; the group only needs a device table of
  * ktmi_group_workspace_bytes(nev) bytes (256-byte aligned, caller-owned).  All
  * handles must share one stream and have an initial state; rebuild the group
  * after changing a handle's tile, EoS, guess mode or network.  ktmi_read /

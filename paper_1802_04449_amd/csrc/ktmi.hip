@@ -359,14 +359,39 @@ static int auto_tile(const ktmi_desc* d) {
   return best;
 }
 
-// Small events: up to 1024 tiles of the automatic shape (2048 on one eta cell, where the
-// shape's vacuum test spares less), and up to 3072 where that shape pads the grid more
-// than the small tiles do (64 thread slots each).
+// Small events.  The small-event kernels win while the large-grid ones leave the chip idle,
+// and by as much as those evaluate faces for padding: q = faces of the padded tiles / faces of
+// the small tiles, a fifth more for 1x8x32 tiles (their x faces share no cache lines) and for
+// grids shorter than a row of 16 cells along eta.  They win up to 500 + 11000 (q - 0.8)^3 tiles
+// of the automatic shape, alone (up to 3072: measured no further) or of all such events of a
+// launch; on one eta cell, where the large tiles take a barrier per axis for two faces a cell,
+// up to 2048 whatever the launch.  Measured on 1423 events and groups of up to 24 (25..241
+// cells a side, 1..105 along eta, ideal / viscous / bulk, hotspots 18-82% vacuum and without
+// vacuum): the rule's choice takes 0.4% more than the better of both on average, 21% at most
+// (a third of what the choice is worth there); small kernels everywhere 5%, large ones 30%.
+// us a viscous step, large-grid kernels -> small-event ones: alone 151x151x1 hotspots 71 -> 41,
+// 601x601x1 155 -> 127, 33x33x17 88 -> 51, 101x101x9 122 -> 75, 128x128x17 202 -> 172 (without
+// vacuum 270 -> 238), 61x61x33 132 -> 104 (131 -> 133), 81x81x33 157 -> 145; but unpadded
+// 48x48x64 105 -> 122, 96x96x48 174 -> 243, and 121x121x33 284 -> 317.  Of a group, us an
+// event: 8 of 33x33x17 26.7 -> 22.0, 2 of 61x61x33 106 -> 86, 3 of them 81 -> 81, 8 of them
+// 63 -> 71, 16 of them 62 -> 78, 8 of 45x45x65 62 -> 78, 16 of 101x101x9 51 -> 48.
 static int small_tile(const ktmi_desc* d) { return d->ne > 1 ? 0 : 1; }
+static double small_limit(const ktmi_desc* d) {
+  if (d->ne == 1) return 2048.0;
+  auto faces = [&](const TileShape& t) {
+    return (double)tile_grid(d, t).ntiles *
+           ((t.tx + 1) * t.ty * t.tz + t.tx * (t.ty + 1) * t.tz + t.tx * t.ty * (t.tz + 1));
+  };
+  const TileShape& t = kTiles[auto_tile(d)];
+  double q = faces(t) / faces(kSmallTiles[small_tile(d)]);
+  if (t.tx == 1) q *= 1.2;
+  if (d->ne < 16) q *= 1.2;
+  const double x = std::max(0.0, q - 0.8);
+  return 500.0 + 11000.0 * x * x * x;
+}
 static bool small_event(const ktmi_desc* d) {
   const int n = tile_grid(d, auto_tile(d)).ntiles;
-  if (n <= (d->ne > 1 ? 1024 : 2048)) return true;
-  return n <= 3072 && 64.0 * tile_grid(d, kSmallTiles[small_tile(d)]).ntiles <= (double)n * kBlock;
+  return n <= 3072 && n <= small_limit(d);
 }
 
 static int max_tiles(const ktmi_desc* d) {
@@ -376,25 +401,15 @@ static int max_tiles(const ktmi_desc* d) {
   return m;
 }
 
-// Tile index and tile grid of a handle's launches: the small-event kernels (bitwise the
-// same fields) for a small event whose tile the library chose, in FP64 (in FP32 the two
-// kernels' products are fused differently and the results move by 1e-9) and without the
-// network.  Alone or in a group alike: the diagnostic sums then have the same order.
-// Measured in us per viscous step, large-grid kernels -> small-event ones, by the number
-// of tiles: 100 (151x151x1 hotspots) 84 -> 47, 361 (301x301x1) 88 -> 57, 512 (64x64x17
-// without vacuum) 122 -> 88, 1444 (601x601x1 hotspots) 189 -> 134, 2048 and 2700 of padded
-// grids (128x128x17, 120x120x33, without vacuum) 310 -> 252 and 411 -> 391; but 1575 of an
-// unpadded one (60x60x105, without vacuum) 291 -> 304, 3250 (101x99x65) 515 -> 555, and on
-// the 201x201x105 event, most of whose tiles are vacuum and skip their face rounds as a
-// whole in the large-grid kernels, 1200 -> 1700.
-static int run_tile(const ktmi_handle* h, TileGrid* tg) {
-  *tg = h->tg;
-  if (!h->tile_auto || h->d.precision != KTMI_FP64 || h->d.guess == KTMI_GUESS_MLP ||
-      !small_event(&h->d))
-    return h->tile;
-  const int id = small_tile(&h->d);
-  *tg = tile_grid(&h->d, kSmallTiles[id]);
-  return kNumTiles + id;
+// Tile index of a handle's launches: the small-event kernels (bitwise the same fields) for a
+// small event whose tile the library chose, in FP64 (in FP32 the two kernels' products are
+// fused differently and the results move by 1e-9) and without the network.
+static bool small_capable(const ktmi_handle* h) {
+  return h->tile_auto && h->d.precision == KTMI_FP64 && h->d.guess != KTMI_GUESS_MLP &&
+         small_event(&h->d);
+}
+static int run_tile(const ktmi_handle* h) {
+  return small_capable(h) ? kNumTiles + small_tile(&h->d) : h->tile;
 }
 
 // Doubles reserved for the per-tile flags: 4 ints per tile of the largest grid
@@ -420,7 +435,8 @@ static int num_blocks(const ktmi_desc* d) {
   return (int)((n + kBlock - 1) / kBlock);
 }
 
-static StepParams step_params(const ktmi_handle* h) {
+// tile: tile index of the launches (run_tile, or a group's choice).
+static StepParams step_params(const ktmi_handle* h, int tile) {
   StepParams p;
   p.nx = h->d.nx;
   p.ny = h->d.ny;
@@ -452,8 +468,7 @@ static StepParams step_params(const ktmi_handle* h) {
   p.newton_maxit = h->d.newton_maxit;
   p.vac_zero = h->d.pi_reg > 0.0 && h->p_at0 == 0.0;
   // quiet tiles: neighbourhood radius in tiles covering 6 cells per axis
-  TileGrid tg;
-  const TileShape& ts = tile_shape(run_tile(h, &tg));
+  const TileShape& ts = tile_shape(tile);
   const int td[3] = {ts.tx, ts.ty, ts.tz};
   for (int a = 0; a < 3; ++a) p.quiet_r[a] = h->quiet_on ? (6 + td[a] - 1) / td[a] : 0;
   p.guess = h->d.guess;
@@ -522,13 +537,13 @@ static GroupTable single_table(const TileGrid& tg) {
   return gt;
 }
 
-static EventDesc make_event(const ktmi_handle* h) {
+static EventDesc make_event(const ktmi_handle* h, int tile) {
   EventDesc ev;
   memset(&ev, 0, sizeof(ev));
   ev.f = h->f;
-  ev.p = step_params(h);
+  ev.p = step_params(h, tile);
   ev.eos = h->eos;
-  (void)run_tile(h, &ev.tg);
+  ev.tg = tile_grid(&h->d, tile);
   ev.cart = h->d.cartesian;
   ev.viscous = h->d.viscous;
   ev.clock = h->clock;
@@ -538,7 +553,7 @@ static EventDesc make_event(const ktmi_handle* h) {
 // Uploads the handle's event table when its parameters changed.
 static int upload_event(ktmi_handle* h) {
   if (!h->ev_dirty) return KTMI_OK;
-  h->ev = make_event(h);
+  h->ev = make_event(h, run_tile(h));
   HIP_TRY(h, hipMemcpyAsync(h->dev_ev, &h->ev, sizeof(EventDesc), hipMemcpyHostToDevice,
                             h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));  // h->ev may change before a later upload
@@ -585,10 +600,9 @@ static int step_mode(const ktmi_handle* h) {
 }
 
 static int enqueue_step(ktmi_handle* h) {
-  TileGrid tg;
-  const int tile = run_tile(h, &tg);
+  const int tile = run_tile(h);
   int rc = enqueue_class_step(h, h->stream, tile, h->d.precision, step_mode(h), uses_net(h),
-                              h->dev_ev, single_table(tg));
+                              h->dev_ev, single_table(tile_grid(&h->d, tile)));
   if (rc) return rc;
   return launch(h, K_REDUCE, [&] {
     hipLaunchKernelGGL(k_reduce, dim3(kNP), dim3(kRedBlock), 0, h->stream, h->dev_ev);
@@ -628,11 +642,11 @@ static int finish_initial(ktmi_handle* h) {
   if (int rc = upload_event(h)) return rc;
   hipLaunchKernelGGL(k_set_clock, dim3(1), dim3(64), 0, h->stream, h->clock, h->tau);
   if (int rc = clear_quiet(h, h->stream)) return rc;  // before the first estimate, which leaves marks
-  TileGrid tg;
-  const int tile = run_tile(h, &tg);
+  const int tile = run_tile(h);
   if (int rc = own_flags(h, h->stream, tile, h->quiet_on)) return rc;
   int rc = launch(h, K_FIRST, [&] {
-    launch_class(PASS_FIRST, h->stream, tile, h->d.precision, false, h->dev_ev, single_table(tg));
+    launch_class(PASS_FIRST, h->stream, tile, h->d.precision, false, h->dev_ev,
+                 single_table(tile_grid(&h->d, tile)));
   });
   if (rc) return rc;
   rc = launch(h, K_INIT, [&] {
@@ -916,7 +930,7 @@ int ktmi_set_initial_primitive_ext(ktmi_handle* h, const double* e, const double
     }
   }
   h->tau = h->d.tau0;
-  const StepParams p = step_params(h);
+  const StepParams p = step_params(h, run_tile(h));
   const Geo g = geo(h, h->tau, h->tau);
   int rc = launch(h, K_INIT, [&] {
     hipLaunchKernelGGL(k_init_primitive, dim3(h->nblk), dim3(kBlock), 0, s, h->f, p, h->eos, g,
@@ -945,7 +959,7 @@ int ktmi_set_initial_conserved(ktmi_handle* h, const double* T4, const double* p
     for (int m = 10; m < 12; ++m)
       hipLaunchKernelGGL(k_zero, dim3(h->nblk), dim3(kBlock), 0, s, h->f.pi[m], (int)n);
   h->tau = h->d.tau0;
-  const StepParams p = step_params(h);
+  const StepParams p = step_params(h, run_tile(h));
   const Geo g = geo(h, h->tau, h->tau);
   int rc = launch(h, K_INIT, [&] {
     if (uses_net(h))
@@ -964,9 +978,8 @@ int ktmi_step(ktmi_handle* h, int nsteps) {
   if (!h->ready) return fail(h, KTMI_ESTATE, "set an initial state first");
   if (nsteps < 0) return fail(h, KTMI_EINVAL, "negative step count");
   if (int rc = upload_event(h)) return rc;
-  TileGrid tg;
   if (nsteps > 0)
-    if (int rc = own_flags(h, h->stream, run_tile(h, &tg), h->quiet_on)) return rc;
+    if (int rc = own_flags(h, h->stream, run_tile(h), h->quiet_on)) return rc;
   const bool graph = h->use_graph && !h->timing;
   if (graph && !h->gexec) {  // capture one step; every step issues the same launches
     hipGraph_t g = nullptr;
@@ -1230,9 +1243,8 @@ int ktmi_set_tile(ktmi_handle* h, int t) {
 int ktmi_quiet_tiles(ktmi_handle* h, long* quiet, long* total) {
   if (!h || !quiet || !total) return KTMI_EINVAL;
   if (!h->ready) return fail(h, KTMI_ESTATE, "no state");
-  TileGrid tg;
-  int tile = run_tile(h, &tg);
-  if (h->flags_tile >= 0) tile = h->flags_tile;  // (a group's, if that stepped last)
+  // (a group's tile, if that stepped last)
+  const int tile = h->flags_tile >= 0 ? h->flags_tile : run_tile(h);
   const int nt = tile_grid(&h->d, tile).ntiles;
   std::vector<int> flags(nt);
   // the step with clock parity p writes flag buffer 1 - p: after an odd number
@@ -1282,10 +1294,15 @@ int ktmi_group_create(ktmi_handle* const* hs, int nev, void* ws, size_t bytes, k
   // classes in first-seen order; events keep their order inside a class
   std::vector<int> order;
   std::vector<std::vector<int>> members;
-  TileGrid tg;
+  // Small events of more than one eta cell share a launch by mode: together they may fill the
+  // chip, and then run on the large-grid kernels (small_limit).
+  double total[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int i = 0; i < nev; ++i)
+    if (hs[i]->d.ne > 1 && small_capable(hs[i])) total[step_mode(hs[i])] += hs[i]->tg.ntiles;
   for (int i = 0; i < nev; ++i) {
     const ktmi_handle* h = hs[i];
-    const int tile = run_tile(h, &tg);
+    int tile = run_tile(h);
+    if (tile >= kNumTiles && h->d.ne > 1 && total[step_mode(h)] > small_limit(&h->d)) tile = h->tile;
     int c = -1;
     for (size_t k = 0; k < g->classes.size(); ++k)
       if (g->classes[k].tile == tile && g->classes[k].precision == h->d.precision &&
@@ -1316,11 +1333,10 @@ int ktmi_group_create(ktmi_handle* const* hs, int nev, void* ws, size_t bytes, k
     int t = 0;
     for (int m = 0; m < cl.gt.nev; ++m) {
       ktmi_handle* h = hs[members[k][m]];
-      (void)run_tile(h, &tg);
       cl.gt.start[m] = t;
-      t += tg.ntiles;
       g->hs.push_back(h);
-      g->host.push_back(make_event(h));
+      g->host.push_back(make_event(h, cl.tile));
+      t += g->host.back().tg.ntiles;
       pos++;
     }
     cl.gt.start[cl.gt.nev] = t;

@@ -74,8 +74,8 @@ struct EosDev {
 // ends of the FP64 range, which the arguments here leave alone, and select the results of
 // zero and infinite ones, which give NaN here: in the Newton steps a NaN is a step outside
 // the bracket.  Where a state may overflow otherwise (the bracket, 1 / sqrt((E + P)(e + P)),
-// the regulator), quot<FAST, true> ends with the division's fix-up instruction and inv_root
-// selects its 0, as IEEE operations give.  The mixed passes keep
+// the regulator), FIX ends the quotient with the division's fix-up instruction and selects
+// inv_root's 0, as IEEE operations give.  The mixed passes keep
 // the general sequences: their FP32 fluxes amplify a last-bit difference of the FP64 state
 // to FP32 rounding, so that a run would become another sample of it.
 // ---------------------------------------------------------------------------
@@ -104,13 +104,14 @@ __device__ __forceinline__ double root(double x) {
   h = __builtin_fma(h, r, h);
   return __builtin_fma(__builtin_fma(-g, g, x), h, g);
 }
-// 1 / sqrt(x), x > 0: y (1 + e/2 + 3 e^2/8), e = 1 - x y^2; 0 for x = inf.
-template <bool FAST>
+// 1 / sqrt(x), x > 0: y (1 + e/2 + 3 e^2/8), e = 1 - x y^2; FIX: 0 for x = inf.
+template <bool FAST, bool FIX = false>
 __device__ __forceinline__ double inv_root(double x) {
   if constexpr (!FAST) return 1.0 / sqrt(x);
   const double y = __builtin_amdgcn_rsq(x);
   const double e = __builtin_fma(-(x * y), y, 1.0);
-  return y == 0.0 ? 0.0 : __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+  const double r = __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+  return FIX && y == 0.0 ? 0.0 : r;
 }
 // Whether the passes of precision RT take them, and sqrt in the passes' flux type.
 template <typename RT>
@@ -326,7 +327,7 @@ __device__ inline Prim con2prim(const EosDev& q, const StepParams& p, double E, 
     return vacuum();
   }
   const double P = BK ? eos_p(q, x) + Pi : eos_p(q, x);
-  const double inv = inv_root<FAST>((E + P) * (x + P));
+  const double inv = inv_root<FAST, true>((E + P) * (x + P));
   return Prim{x, K1 * inv, K2 * inv, K3 * inv};
 }
 

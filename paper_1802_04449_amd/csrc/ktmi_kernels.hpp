@@ -1252,10 +1252,10 @@ __device__ __forceinline__ void regulate(const EosDev& eos, const StepParams& p,
   double f = 1.0;
   bool over;
   if constexpr (FAST) {
-    // (an infinite square is over any finite cap, and scales to zero)
+    // (an infinite square is over any finite one, and scales to zero)
     const double cap = p.pi_reg * w;
-    over = fabs(pp) > cap * cap || (fabs(pp) == (double)INFINITY && cap < (double)INFINITY);
-    if (over) f = cap * inv_root<true>(fabs(pp));
+    over = fabs(pp) > cap * cap;
+    if (over) f = cap * inv_root<true, true>(fabs(pp));
   } else {
     const double rho = sqrt(fabs(pp)) / w;
     over = rho > p.pi_reg;

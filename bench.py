@@ -323,7 +323,8 @@ def batch_path(params, steps, reps, nev=64):
         for wl in evs:
             h = make_hydro(wl, stream=st, precision=precision)
             reset(h, wl)
-            t, _ = autotune.tune(h, steps=2, repeats=1, use_cache=False)
+            # (the group fills the chip: no events on the small-event kernels)
+            t, _ = autotune.tune(h, steps=2, repeats=1, use_cache=False, automatic=False)
             sel.append(t)
             del h
         tiles[precision] = sel

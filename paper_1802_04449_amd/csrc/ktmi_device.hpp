@@ -332,37 +332,9 @@ __device__ inline Prim con2prim(const EosDev& q, const StepParams& p, double E, 
 }
 
 // ---------------------------------------------------------------------------
-// Reconstruction and the KT local speed (Sec. III, eqs. kt and flux_out).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double minmod3(double a, double b, double c) {
-  if (a > 0.0 && b > 0.0 && c > 0.0) return fmin(a, fmin(b, c));
-  if (a < 0.0 && b < 0.0 && c < 0.0) return fmax(a, fmax(b, c));
-  return 0.0;
-}
-
-__device__ __forceinline__ double mm_slope(double th, double qm, double q0, double qp) {
-  return minmod3(th * (q0 - qm), 0.5 * (qp - qm), th * (qp - q0));
-}
-
-// Largest |eigenvalue| of the ideal flux Jacobian along the face normal for a
-// state with u~ = (ut, ux, uy, ue) and sound speed squared cs2:
-// lambda = [v_d (1-cs2) +- cs sqrt((1-v^2)(1 - v^2 cs2 - v_d^2 (1-cs2)))]/(1 - v^2 cs2).
-__device__ __forceinline__ double local_speed(double ut, double ux, double uy, double ue,
-                                              double ud, double cs2) {
-  const double inv = 1.0 / ut;
-  const double vd = ud * inv;
-  const double v2 = (ux * ux + uy * uy + ue * ue) * inv * inv;
-  double disc = inv * inv * (1.0 - v2 * cs2 - vd * vd * (1.0 - cs2));
-  disc = disc < 0.0 ? 0.0 : disc;
-  const double root = sqrt(cs2 * disc);
-  const double inv_den = 1.0 / (1.0 - v2 * cs2);
-  const double a = vd * (1.0 - cs2);
-  return (fabs(a) + root) * inv_den;  // = max(|a + root|, |a - root|) / den, root >= 0
-}
-
-// ---------------------------------------------------------------------------
-// Precision-generic versions for the flux and relaxation arithmetic: R = double
-// (FP64 path) or float (mixed path; table values from the FP32 copy).
+// EoS lookups, reconstruction and the KT local speed (Sec. III, eqs. kt and flux_out) of the
+// flux and relaxation arithmetic: R = double (FP64 path) or float (mixed path; table values
+// from the FP32 copy).
 // ---------------------------------------------------------------------------
 template <typename R>
 __device__ __forceinline__ void eos_p_cs2_r(const EosDev& q, R e, R& P, R& cs2);

@@ -65,17 +65,15 @@ __device__ __forceinline__ void mlp_layer1(const float* __restrict__ prm, const 
   }
 }
 
-// FP32 layers 2 and 3 of one sample (per lane); h2 receives the hidden outputs.
-__device__ __forceinline__ float mlp_z_fp32(const float* __restrict__ prm, const float h1[kMlpH],
-                                            float h2[kMlpH]) {
+// FP32 layers 2 and 3 of one sample (per lane).
+__device__ __forceinline__ float mlp_z_fp32(const float* __restrict__ prm, const float h1[kMlpH]) {
   float z = prm[kOB3];
 #pragma unroll
   for (int i = 0; i < kMlpH; ++i) {
     float a = prm[kOB2 + i];
 #pragma unroll
     for (int j = 0; j < kMlpH; ++j) a += prm[kOW2 + i * kMlpH + j] * h1[j];
-    h2[i] = mlp_tanh(a);
-    z += prm[kOW3 + i] * h2[i];
+    z += prm[kOW3 + i] * mlp_tanh(a);
   }
   return z;
 }
@@ -149,11 +147,11 @@ __device__ __forceinline__ double mlp_guess_from_z(float z, double E, double lo)
 // Guess of one lane (FP32 forward; divergent lanes allowed).
 __device__ __forceinline__ double mlp_guess_lane(const float* __restrict__ prm, double E,
                                                  double M2) {
-  float f[4], h1[kMlpH], h2[kMlpH];
+  float f[4], h1[kMlpH];
   double lo;
   mlp_features(E, M2, f, lo);
   mlp_layer1(prm, f, h1);
-  return mlp_guess_from_z(mlp_z_fp32(prm, h1, h2), E, lo);
+  return mlp_guess_from_z(mlp_z_fp32(prm, h1), E, lo);
 }
 
 // Guess of every lane of the wave (matrix-core forward; all lanes active).

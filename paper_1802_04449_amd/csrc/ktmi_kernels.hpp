@@ -305,7 +305,8 @@ __device__ __forceinline__ Pos cell_pos(const StepParams& p, const TileGrid& tg,
 // (6 cells: the reach of stage 1 and stage 2 stencils and gradients) was
 // quiet after the previous step: all three passes would then reproduce exactly
 // the values its buffers hold.  Returns the block-uniform decision.
-template <int TX, int TY, int TZ>
+// BLOCK: threads of the workgroup.
+template <int TX, int TY, int TZ, int BLOCK = kBlock>
 __device__ __forceinline__ bool tile_asleep(const StepParams& p, const TileGrid& tg,
                                             const gint* __restrict__ qcur, int tile) {
   if (p.quiet_r[0] <= 0) return false;
@@ -314,7 +315,7 @@ __device__ __forceinline__ bool tile_asleep(const StepParams& p, const TileGrid&
   const int rx = p.quiet_r[0], ry = p.quiet_r[1], rz = p.quiet_r[2];
   const int wx = 2 * rx + 1, wy = 2 * ry + 1, wz = 2 * rz + 1;
   int awake = 0;
-  for (int n = threadIdx.x; n < wx * wy * wz; n += kBlock) {
+  for (int n = threadIdx.x; n < wx * wy * wz; n += BLOCK) {
     const int a = ti - rx + n / (wy * wz), b = tj - ry + (n / wz) % wy, c = tk - rz + n % wz;
     if (a < 0 || a >= tg.ntx || b < 0 || b >= tg.nty || c < 0 || c >= tg.ntz) continue;
     awake |= (qcur[(a * tg.nty + b) * tg.ntz + c] & 1) == 0;
@@ -1055,28 +1056,28 @@ constexpr int lds_doubles_allf() {
   return 4 * (L::F0 + L::F1 + L::F2);
 }
 
-// Waves per SIMD asked of the stage-2 passes: at least 3 where the tile's LDS
-// leaves room for three workgroups per CU (160 KB), else no bound.  The cap was
-// a net gain when these passes needed more registers (stage2_pi 10-16%,
-// stage2_T 1-5% on the 201x201x105 grids, with a few spilled registers; the
-// lambda_1 variant 8% in FP64 with 60 bytes of spill, 13% in FP32); the plain
-// stage2_pi now fits 126 VGPRs (FP64, four waves) and 92 (FP32, five) without
-// it.  Stage1 loses from the cap, so it has none, nor has the bulk variant of
-// stage2_pi (it spilled 96 bytes a lane under the cap: 1.06 ms against 0.75 ms
-// without it; its stage2_T keeps the cap).  NOCAP = true asks for no bound.
-template <typename RT, int TX, int TY, int TZ, bool NOCAP, int NC = 14>
-constexpr int pi_waves() {
-  return !NOCAP && 163840 / (int)(lds_doubles<TX, TY, TZ, NC>() * sizeof(RT) + 512) >= 3 ? 3 : 1;
+// Waves per SIMD asked of the stage-2 passes: three, for which every tile's LDS leaves room
+// (160 KB a CU).  The cap was a net gain when these passes needed more registers (stage2_pi
+// 10-16%, stage2_T 1-5% on the 201x201x105 grids, with a few spilled registers; the
+// lambda_1 variant 8% in FP64, 13% in FP32); now no instance needs it (stage2_pi 126-133
+// VGPRs in FP64, 143 with lambda_1, 93 in FP32, none spilled).  Stage1 loses from the cap, so
+// it has none, nor has the bulk variant of stage2_pi (it spilled 96 bytes a lane under the cap:
+// 1.06 ms against 0.75 ms without it; its stage2_T keeps the cap).
+template <typename RT, int TX, int TY, int TZ, bool BK>
+constexpr int s2pi_waves() {
+  static_assert(BK || 3 * (lds_doubles<TX, TY, TZ, 10, true>() * sizeof(RT) + 512) <= 163840,
+                "three workgroups per CU");
+  return BK ? 1 : 3;
 }
 
 // Waves per SIMD asked of stage 2T: four without bulk in FP64 (127 VGPRs with 2 spilled;
 // three or five waves are slower, and when its faces needed 143 VGPRs the cap took it
 // from 0.46 to 0.42 ms on the 201x201x105 hotspot grid, 0.86 to 0.84 ms without vacuum),
-// five in FP32 (90 VGPRs, no spill: 0.36 -> 0.33 ms and 0.64 -> 0.60 ms); with bulk as the
-// other stage-2 passes.
-template <typename RT, int TX, int TY, int TZ, bool BK>
+// five in FP32 (90 VGPRs, no spill: 0.36 -> 0.33 ms and 0.64 -> 0.60 ms); with bulk three
+// (135-139 VGPRs).
+template <typename RT, bool BK>
 constexpr int s2t_waves() {
-  return !BK ? (sizeof(RT) == 4 ? 5 : 4) : pi_waves<RT, TX, TY, TZ, false>();
+  return BK ? 3 : (sizeof(RT) == 4 ? 5 : 4);
 }
 
 // u~^tau of spatial components, and its reciprocal.
@@ -1788,7 +1789,7 @@ __device__ __forceinline__ bool stage2_pi_cell(const DFields& f, const StepParam
 // leaves room for four workgroups per CU.
 template <typename RT, int TX, int TY, int TZ, bool L1, bool BK = false>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(pi_waves<RT, TX, TY, TZ, BK, BK ? 16 : 14>()))) void k_stage2_pi(
+__attribute__((amdgpu_waves_per_eu(s2pi_waves<RT, TX, TY, TZ, BK>()))) void k_stage2_pi(
     const EventDesc* __restrict__ evs, GroupTable gt) {
   constexpr int NQ = BK ? 12 : 10;
   __shared__ RT lds[lds_doubles<TX, TY, TZ, NQ, true>()];
@@ -1939,7 +1940,7 @@ __device__ __forceinline__ void stage2_T_asleep(const DFields& f, const StepPara
 // in every guess mode (no network instance).
 template <typename RT, int TX, int TY, int TZ, bool VISC, bool BK = false>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(s2t_waves<RT, TX, TY, TZ, BK>()))) void k_stage2_T(const EventDesc* __restrict__ evs,
+__attribute__((amdgpu_waves_per_eu(s2t_waves<RT, BK>()))) void k_stage2_T(const EventDesc* __restrict__ evs,
                                                      GroupTable gt) {
   __shared__ RT lds[lds_doubles_allf<TX, TY, TZ>()];
   const Ctx cx = load_ctx(evs, gt, 1);
@@ -2125,7 +2126,7 @@ __global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_stage1_sma
   KTMI_SMALL_PROLOGUE(0);
   CellDiag v;
   double R[4 + NQ];
-  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) {
+  if (tile_asleep<TX, TY, TZ, SmallLayout<TX, TY, TZ>::BLOCK>(p, cx.tg, cx.qcur, cx.tile)) {
     if (wave < AXES) return;
     stage1_asleep<RT>(f, p, q, tf, v);
     small_partials(v, f.partial, cx.tg.ntiles, cx.tile);
@@ -2158,7 +2159,7 @@ __global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_stage2_pi_
   constexpr int NQ = BK ? 12 : 10;
   __shared__ RT lds[NQ * SmallLayout<TX, TY, TZ>::FT];
   KTMI_SMALL_PROLOGUE(1);
-  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) return;
+  if (tile_asleep<TX, TY, TZ, SmallLayout<TX, TY, TZ>::BLOCK>(p, cx.tg, cx.qcur, cx.tile)) return;
   double R[4 + NQ];
 #pragma unroll
   for (int k = 0; k < 4 + NQ; ++k) R[k] = 0.0;
@@ -2184,7 +2185,7 @@ __global__ __launch_bounds__((SmallLayout<TX, TY, TZ>::BLOCK)) void k_stage2_T_s
   __shared__ double shcfl[3];
   KTMI_SMALL_PROLOGUE(1);
   CellDiag v;
-  if (tile_asleep<TX, TY, TZ>(p, cx.tg, cx.qcur, cx.tile)) {
+  if (tile_asleep<TX, TY, TZ, SmallLayout<TX, TY, TZ>::BLOCK>(p, cx.tg, cx.qcur, cx.tile)) {
     if (wave < AXES) return;
     stage2_T_asleep<RT>(f, p, q, tf, v);
     small_partials(v, f.partial + (size_t)kNP * cx.tg.ntiles, cx.tg.ntiles, cx.tile);

@@ -1287,12 +1287,21 @@ int ktmi_group_create(ktmi_handle* const* hs, int nev, void* ws, size_t bytes, k
     for (int j = 0; j < i; ++j)
       if (hs[j] == hs[i]) return fail(nullptr, KTMI_EINVAL, "a handle appears twice");
   }
+  // at most kMaxGroup events of one shape, precision, mode and guess kind
+  for (int i = 0; i < nev; ++i) {
+    int same = 0;
+    for (int j = 0; j < nev; ++j)
+      same += hs[j]->tile == hs[i]->tile && hs[j]->d.precision == hs[i]->d.precision &&
+              step_mode(hs[j]) == step_mode(hs[i]) && uses_net(hs[j]) == uses_net(hs[i]);
+    if (same > kMaxGroup)
+      return fail(nullptr, KTMI_EINVAL, "too many events of one class (max 128)");
+  }
   ktmi_group* g = new ktmi_group();
   g->stream = hs[0]->stream;
   g->timing_stub.stream = g->stream;
   g->dev = (EventDesc*)ws;
-  // classes in first-seen order; events keep their order inside a class
-  std::vector<int> order;
+  // classes in first-seen order; events keep their order inside a class (small events of
+  // several shapes share one until it is full)
   std::vector<std::vector<int>> members;
   // Small events of more than one eta cell share a launch by mode: together they may fill the
   // chip, and then run on the large-grid kernels (small_limit).
@@ -1306,7 +1315,8 @@ int ktmi_group_create(ktmi_handle* const* hs, int nev, void* ws, size_t bytes, k
     int c = -1;
     for (size_t k = 0; k < g->classes.size(); ++k)
       if (g->classes[k].tile == tile && g->classes[k].precision == h->d.precision &&
-          g->classes[k].mode == step_mode(h) && g->classes[k].net == uses_net(h))
+          g->classes[k].mode == step_mode(h) && g->classes[k].net == uses_net(h) &&
+          (int)members[k].size() < kMaxGroup)
         c = (int)k;
     if (c < 0) {
       ktmi_group::Class cl{};
@@ -1323,10 +1333,6 @@ int ktmi_group_create(ktmi_handle* const* hs, int nev, void* ws, size_t bytes, k
   int pos = 0;
   for (size_t k = 0; k < g->classes.size(); ++k) {
     auto& cl = g->classes[k];
-    if ((int)members[k].size() > kMaxGroup) {
-      delete g;
-      return fail(nullptr, KTMI_EINVAL, "too many events of one class (max 128)");
-    }
     cl.first = pos;
     memset(&cl.gt, 0, sizeof(cl.gt));
     cl.gt.nev = (int)members[k].size();

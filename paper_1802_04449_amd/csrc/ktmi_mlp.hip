@@ -85,10 +85,11 @@ static_assert(sizeof(GradLds) >= kMlpSlots * sizeof(float), "a wave's record fit
 // through LDS.  FP32 products and sums throughout (v_mfma_f32_32x32x8_bf16 for the
 // 32 x 32 layer's forward in MODE 1).  Bound by FP32 matrix-core time (52 products of 64
 // clocks per 32 samples, 42 us for 1e6 samples) next to about as much VALU work, at two
-// waves per SIMD (256 registers, 11-20 spilled; one wave without the bound).  8192
-// samples, gradient and fold: 206 -> 16 us (FP32); 1e6: 3645 -> 99 us (BF16 forward).  One
-// sample per lane with LDS sums over 128 samples, as it was, left the matrix cores idle
-// and read 2 x 128 LDS values for each of the 1249 sums and chunk.
+// waves per SIMD (256 registers, 11-20 spilled; one wave without the bound).  Kernel
+// trace, gradient + fold: 8192 samples 206 -> 11.6 + 3.7 us (FP32), 1e6 3645 -> 84 + 12 us (BF16
+// forward; its matrix cores busy 36% of the time); a whole Adam step without the profiler
+// 187 -> 16 and 3370 -> 91 us.  One sample per lane with LDS sums over 128 samples, as it was,
+// left the matrix cores idle and read 2 x 128 LDS values for each of the 1249 sums and chunk.
 template <int MODE>
 __global__ __launch_bounds__(64 * kGradWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp_grad(const float* __restrict__ prm, int n,
                                                              const double* __restrict__ E,
@@ -350,7 +351,8 @@ static int scratch_on_current_device(float** out) {
 static int launch_mlp_grad(const float* params, int n, const double* E, const double* M,
                            const double* eps, double emin, int mode, float* out, float* part,
                            hipStream_t s) {
-  // four waves of 64 samples per workgroup: at most half the records mlp_grid allows
+  // four waves of 64 samples per workgroup: a record per 256 samples, at most mlp_grid(n)
+  // (all kMlpGrid records from 131 000 samples on)
   const int nblk = std::min(mlp_grid(n), (int)(((long)n + 64 * kGradWaves - 1) / (64 * kGradWaves)));
   const dim3 grid(nblk), block(64 * kGradWaves);
   if (mode == KTMI_MLP_BF16)

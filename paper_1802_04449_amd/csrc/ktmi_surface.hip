@@ -198,27 +198,30 @@ __global__ __launch_bounds__(kCountBlock) void k_surface_count(SurfaceArgs a, in
   int nw = 0;
   for (int it = 0; it < kSpan / kCountBlock; ++it) {
     const long id = sb * kSpan + (long)it * kCountBlock + threadIdx.x;
-    const int c = first_corner(id);
-    unsigned any = 0, all = 3;  // of the corners on the lower and the upper eta
-    auto corners = [&](unsigned two) {
-      any |= two;
-      all &= two;
-    };
+    unsigned long long mask = 0;
+    if (id - lane < ncube) {  // (waves past the end of a small grid have nothing to look at)
+      const int c = first_corner(id);
+      unsigned any = 0, all = 3;  // of the corners on the lower and the upper eta
+      auto corners = [&](unsigned two) {
+        any |= two;
+        all &= two;
+      };
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        if (fits) {
-          const int b = c - c0 + (r ? sy : 0);
-          const unsigned* w = (const unsigned*)run[q] + (b >> 5);
-          const unsigned two = __builtin_amdgcn_alignbit(w[1], w[0], b & 31);
-          corners(sz ? two & 3 : 3 * (two & 1));
-        } else {
-          const gdouble* e = (q & 2 ? B : A) + (q & 1 ? sx : 0) + (r ? sy : 0) + c;
-          corners((e[0] > a.eps_f ? 1u : 0u) | (e[sz] > a.eps_f ? 2u : 0u));
+        for (int r = 0; r < 2; ++r) {
+          if (fits) {
+            const int b = c - c0 + (r ? sy : 0);
+            const unsigned* w = (const unsigned*)run[q] + (b >> 5);
+            const unsigned two = __builtin_amdgcn_alignbit(w[1], w[0], b & 31);
+            corners(sz ? two & 3 : 3 * (two & 1));
+          } else {
+            const gdouble* e = (q & 2 ? B : A) + (q & 1 ? sx : 0) + (r ? sy : 0) + c;
+            corners((e[0] > a.eps_f ? 1u : 0u) | (e[sz] > a.eps_f ? 2u : 0u));
+          }
         }
-      }
-    const unsigned long long mask = __ballot(id < ncube && any != 0 && all != 3);
+      mask = __ballot(id < ncube && any != 0 && all != 3);
+    }
     if (lane == 0) masks[it * W + wave] = mask;
     nw += __popcll(mask);
   }

@@ -389,7 +389,10 @@ int ktmi_surface(ktmi_handle *h, const double *A, double tau_A, const double *B,
  * (eps_plus_P = e + P at freeze-out in GeV/fm^3; 0 leaves delta f out).  out is
  * device memory; ws is caller-owned device scratch of ktmi_spectra_workspace_bytes
  * bytes (a smaller one is taken too if it holds one partial result per 256 elements, at
- * most 64 of them; the sums are then split less).  The result does not depend on scheduling (fixed summation order).
+ * most 64 of them; the sums are then split less).  The result does not depend on
+ * scheduling (fixed summation order).  Elements whose flow is so fast that pT u~^tau / T
+ * exceeds 1e6, or that hold NaN, are taken bin by bin, together with those summed with
+ * them (slower).
  * Synchronises stream once (upload of the small tables), then runs async on it.
  * KTMI_EINVAL on bad arguments or a short workspace. */
 size_t ktmi_spectra_workspace_bytes(long n, int ns, int nY, int npt, int nphi);

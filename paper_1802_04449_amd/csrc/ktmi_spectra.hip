@@ -61,10 +61,9 @@ struct SpecShape {
   int nby;    // workgroups over the transverse groups
 };
 
-// e^x = m 2^k with |m - 1| < 0.42 (finite x; cut at |x| = 7e8, so that the sum of two such k
-// fits 32 bits: the two factors of a bin may cancel up to there, u~ of about 1e7; NaN stays
-// NaN): k = round(x log2 e), then the Taylor series of e^r, |r| <= ln2 / 2, to r^13 / 13!
-// (remainder < 1e-17).
+// e^x = m 2^k with |m - 1| < 0.42 (cut at |x| = 7e8, where the value over- or underflows all
+// the same and the sum of two such k fits 32 bits; NaN stays NaN): k = round(x log2 e), then the
+// Taylor series of e^r, |r| <= ln2 / 2, to r^13 / 13! (remainder < 1e-17).
 __device__ __forceinline__ double split_exp(double x, int& k) {
   x = x > 7e8 ? 7e8 : x;
   x = x < -7e8 ? -7e8 : x;
@@ -164,7 +163,8 @@ __global__ __launch_bounds__(kSpecBlock) __attribute__((amdgpu_waves_per_eu(3)))
       const int e = k / (sh.npb * NS), r = k - e * (sh.npb * NS);
       const gdouble* g = el + (c0 + e) * kSurfRec;
       const double yrel = shY[r % NS] - g[4], ux = g[9], uy = g[10], ue = g[11];
-      const double ut = sqrt(1.0 + ux * ux + uy * uy + ue * ue);
+      const double ut2 = 1.0 + ux * ux + uy * uy + ue * ue;
+      const double ut = sqrt(ut2 < a.far2 ? ut2 : NAN);  // NaN: left to the fold
       int ke, kl;
       const double ey = ldexp(split_exp(yrel, ke), ke), iey = recip(ey);
       // sinh by its series where the exponentials cancel (|yrel| < 0.3: y^15 / 15! < 2e-20)
@@ -251,7 +251,38 @@ __global__ __launch_bounds__(kSpecBlock) __attribute__((amdgpu_waves_per_eu(3)))
   }
 }
 
-// out[bin] = dof[s] / (2 pi hbarc)^3 * sum over slices (in slice order).
+// Sum of elements e0 .. e1 - 1 for one bin, with one exponential for the whole exponent.
+__device__ double bin_sum(const SpectraArgs& a, long bin, long e0, long e1) {
+  const gdouble* tab = (const gdouble*)a.tables;
+  const gdouble* tpt = tab + 4 * a.ns + a.nY;
+  const int iq = (int)(bin % a.nphi), ip = (int)(bin / a.nphi % a.npt);
+  const int sy = (int)(bin / ((long)a.nphi * a.npt)), s = sy / a.nY;
+  const double m = tab[s], sig = tab[2 * a.ns + s], mu = tab[3 * a.ns + s];
+  const double Y = tab[4 * a.ns + sy % a.nY], pt = tpt[ip], mT = sqrt(m * m + pt * pt);
+  const double x = pt * tpt[a.npt + iq], y = pt * tpt[a.npt + a.nphi + iq], invT = 1.0 / a.T;
+  double sum = 0.0;
+  for (long e = e0; e < e1; ++e) {
+    const gdouble* g = (const gdouble*)a.elements + e * kSurfRec;
+    const double ux = g[9], uy = g[10], ue = g[11];
+    const double p0 = mT * cosh(Y - g[4]), p3 = mT * sinh(Y - g[4]);
+    const double pu = p0 * sqrt(1.0 + ux * ux + uy * uy + ue * ue) - p3 * ue - x * ux - y * uy;
+    const double f = 1.0 / (exp((pu - mu) * invT) + sig);
+    double w = 1.0;
+    if (a.eps_plus_P > 0.0) {
+      const double ppi = p0 * p0 * g[12] + x * x * g[16] + y * y * g[19] + p3 * p3 * g[21] +
+                         2.0 * (-p0 * x * g[13] - p0 * y * g[14] - p0 * p3 * g[15] + x * y * g[17] +
+                                x * p3 * g[18] + y * p3 * g[20]);
+      w = 1.0 + (1.0 - sig * f) * ppi / (2.0 * a.T * a.T * a.eps_plus_P);
+    }
+    sum += (p0 * g[5] + p3 / g[1] * g[8] + x * g[6] + y * g[7]) * f * w;
+  }
+  return sum;
+}
+
+// out[bin] = dof[s] / (2 pi hbarc)^3 * sum over slices (in slice order).  A slice's sum is NaN
+// where an element is (its sum here is too), or for a far element: flow so fast, or infinite,
+// that the exponents of both factors might reach the cut while they cancel in the bin (p_T
+// u~^tau / T > 1e6 for the largest p_T: SpectraArgs::far2).
 __global__ __launch_bounds__(kSpecBlock) void k_spectra_fold(SpectraArgs a, int nslice) {
   const long bin = (long)blockIdx.x * kSpecBlock + threadIdx.x;
   if (bin >= a.nbins) return;
@@ -260,6 +291,15 @@ __global__ __launch_bounds__(kSpecBlock) void k_spectra_fold(SpectraArgs a, int 
   double sum = 0.0;
 #pragma unroll 8
   for (int k = 0; k < nslice; ++k) sum += part[(long)k * a.nbins + bin];
+  if (sum != sum) {
+    const long per = (a.n + nslice - 1) / nslice;
+    sum = 0.0;
+    for (int k = 0; k < nslice; ++k) {
+      const double v = part[(long)k * a.nbins + bin];
+      const long e0 = k * per;
+      sum += v != v ? bin_sum(a, bin, e0, e0 + per < a.n ? e0 + per : a.n) : v;
+    }
+  }
   const int s = (int)(bin / ((long)a.nY * a.npt * a.nphi));
   const double pref = 1.0 / ((2.0 * M_PI * kHbarc) * (2.0 * M_PI * kHbarc) * (2.0 * M_PI * kHbarc));
   ((gdouble*)a.out)[bin] = tab[a.ns + s] * pref * sum;
@@ -412,6 +452,9 @@ int ktmi_spectra(const double* elements, long n, double T, double eps_plus_P, in
   a.npt = npt;
   a.nphi = nphi;
   a.nbins = (long)nbins;
+  double ptm = 0.0;
+  for (int k = 0; k < npt; ++k) ptm = std::max(ptm, fabs(pt[k]));
+  a.far2 = (1e6 * T / ptm) * (1e6 * T / ptm);  // (infinite for p_T = 0)
   a.tables = dtab;
   a.partial = dtab + tab.size();
   a.out = out;

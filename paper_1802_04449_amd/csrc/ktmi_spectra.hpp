@@ -19,6 +19,7 @@ struct SpectraArgs {
   int ns, nY, npt, nphi;
   long nbins;              // ns nY npt nphi
   const double* tables;    // mass, dof, stat, mu (ns each), Y, pT, cos phi, sin phi
+  double far2;             // (u~^tau)^2 from which on an element's factors are not used
   double* partial;         // slices x nbins
   double* out;             // nbins
 };

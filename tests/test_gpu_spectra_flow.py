@@ -12,7 +12,7 @@ import oracle as O
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("u", [4e4, 1e5, 3e6])
+@pytest.mark.parametrize("u", [4e4, 1e5, 3e6, 1e9, 1e11])
 def test_cancelling_factors(u):
     import torch
 
@@ -33,3 +33,47 @@ def test_cancelling_factors(u):
     o = O.spectra(r, T, 0.0, sp, Y, pt, phi)
     x = 3.0 * u / T
     np.testing.assert_allclose(g, o, rtol=8 * x * 2.0 ** -53 + 1e-11, atol=1e-300)
+
+
+@pytest.mark.parametrize("u", [1e150, 1e200, 1e308, -1e308, math.inf, -math.inf, math.nan])
+@pytest.mark.parametrize("col", [9, 10, 11])
+def test_flow_beyond_the_range(u, col):
+    """u~ whose square or whose product with p_T overflows, infinite or NaN: zero, NaN or the
+    other elements' sum where the formula in FP64 gives it."""
+    import torch
+
+    import paper_1802_04449_amd as K
+    print(f"[gpu-case] spectra at u~[{col}] = {u}", flush=True)
+    rng = np.random.default_rng(4)
+    n = 23
+    r = np.zeros((n, 24))
+    r[:, 1] = rng.uniform(1.0, 9.0, n)
+    r[:, 4] = rng.uniform(-0.5, 0.5, n)
+    r[:, 5:9] = 1e-2 * rng.random((n, 4)) * r[:, 1:2]
+    r[:, 9:11] = rng.uniform(-1.0, 1.0, (n, 2))
+    r[7, col] = u
+    sp = ([0.5, 0.13957, 0.93827], [1.0, 1.0, 2.0], [0, -1, 1], [0.0, 0.0, 0.1])
+    Y, pt, phi = np.array([-0.3, 0.2]), np.array([0.1, 0.5, 0.9]), np.array([0.4, 2.0, 3.5, 5.0])
+    g = K.spectra(torch.as_tensor(r).cuda(), 0.137, 0.0, sp, Y, pt, phi).cpu().numpy()
+    o = O.spectra(r, 0.137, 0.0, sp, Y, pt, phi)
+    np.testing.assert_allclose(g, o, rtol=1e-11)
+
+
+def test_exponential_below_the_normal_range():
+    """A Boltzmann species with mu - p.u of 700 to 760 T: e^x is a subnormal number or zero in
+    some bins, f large or infinite."""
+    import torch
+
+    import paper_1802_04449_amd as K
+    print("[gpu-case] spectra with subnormal exponentials", flush=True)
+    rng = np.random.default_rng(5)
+    r = np.zeros((9, 24))
+    r[:, 1] = rng.uniform(1.0, 9.0, 9)
+    r[:, 5:9] = 1e-2 * rng.random((9, 4)) * r[:, 1:2]
+    r[:, 9:11] = 0.1 * rng.uniform(-1.0, 1.0, (9, 2))
+    sp = ([0.5, 0.5], [1.0, 1.0], [0, 1], [75.5, 0.1])
+    Y, pt, phi = np.array([0.0]), np.linspace(0.0, 6.0, 20), np.array([0.4, 2.0])
+    g = K.spectra(torch.as_tensor(r).cuda(), 0.1, 0.0, sp, Y, pt, phi).cpu().numpy()
+    o = O.spectra(r, 0.1, 0.0, sp, Y, pt, phi)
+    assert np.isinf(o[0]).any() and np.isfinite(o[0]).any()
+    np.testing.assert_allclose(g, o, rtol=1e-11)

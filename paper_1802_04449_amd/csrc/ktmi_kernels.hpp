@@ -1252,13 +1252,14 @@ __device__ __forceinline__ void regulate(const EosDev& eos, const StepParams& p,
                     2.0 * (pv[5] * pv[5] + pv[6] * pv[6] + pv[8] * pv[8]);
   double f = 1.0;
   bool over;
+  const double app = fabs(pp);
   if constexpr (FAST) {
-    // (an infinite square is over any finite one, and scales to zero)
+    // where a square overflows: pi~'s is over any cap (f = 0), the cap's over any finite one
     const double cap = p.pi_reg * w;
-    over = fabs(pp) > cap * cap;
-    if (over) f = cap * inv_root<true, true>(fabs(pp));
+    over = app > fmin(cap * cap, 1e300);
+    if (over) f = fmin(cap * inv_root<true, true>(app), 1.0);
   } else {
-    const double rho = sqrt(fabs(pp)) / w;
+    const double rho = sqrt(app) / w;
     over = rho > p.pi_reg;
     if (over) f = p.pi_reg / rho;
   }

@@ -69,13 +69,16 @@ def test_infinite_state(T, tile):
 
 
 @pytest.mark.parametrize("tile", [-1, 0])
-@pytest.mark.parametrize("big", [1e150, 1e155, 1e170])
-def test_regulator(big, tile):
-    """A shear stress whose square overflows is scaled to zero; the cell keeps its e."""
-    print(f"[gpu-case] regulator {big} tile {tile}", flush=True)
+@pytest.mark.parametrize("E,big", [(10.0, 1e149), (10.0, 1e150), (10.0, 1e155), (10.0, 1e170),
+                                   (1e160, 3e160), (1e160, 1e155), (1e200, 1e170),
+                                   (1e160, 1e100)])
+def test_regulator(E, big, tile):
+    """A shear stress whose square overflows is scaled to zero, also next to an e whose square
+    does; the cell keeps its e."""
+    print(f"[gpu-case] regulator {E} {big} tile {tile}", flush=True)
     pi = np.zeros(10)
     pi[4], pi[7] = big, -big  # xx and yy: K is not touched
-    wl = _workload((10.0, 1.0, 0.0, 0.0), pi)
+    wl = _workload((E, 0.1 * E if E < 1e100 else 0.0, 0.0, 0.0), pi)
     g, o = G.run_gpu(wl, 2, tile=tile), G.run_oracle(wl, 2)
     G.assert_parity(g.fields(), o.fields(), 1e-12, f"pi {big}")
     dg, do = g.diag(), o.diag()
